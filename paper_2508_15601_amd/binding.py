@@ -1,7 +1,9 @@
-"""ctypes binding of libtm_w4.so.  Same names as the C ABI; tensors are torch CUDA(=HIP) tensors.
+"""Binding of libtm_w4.so.  Same names as the C ABI; tensors are torch CUDA(=HIP) tensors.
 
-The library is loaded from this directory and nowhere else; if it is missing the import of any entry point fails
-loudly (there is no fallback path of any kind)."""
+The entry points that a serving loop calls per step (the GEMMs, the cache append, attention) go through the native
+extension tm_calls (csrc/tm_calls.cpp), which checks the tensors and calls the C ABI; everything else goes through ctypes.
+Both are loaded from this directory and nowhere else; if one is missing the first use of any entry point fails loudly
+(there is no fallback path of any kind)."""
 from __future__ import annotations
 
 import ctypes
@@ -10,6 +12,7 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libtm_w4.so")
 _lib = None
+_calls = None              # the native extension, loaded with the library
 
 TM_OK = 0
 
@@ -30,7 +33,7 @@ class TmEpilogue(ctypes.Structure):
 
 def load_library():
     """dlopen libtm_w4.so (built by paper_2508_15601_amd/build.py) and declare every entry point."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     # PyTorch-ROCm ships its own HIP runtime (same soname as the system one).  Import torch first so that the
@@ -127,8 +130,16 @@ def load_library():
     lib.tm_last_error.argtypes = []
     lib.tm_version.restype = c.c_char_p
     lib.tm_version.argtypes = []
+    from . import tm_calls
+    tm_calls.set_error(TmError)
+    _calls = tm_calls
     _lib = lib
     return lib
+
+
+def _native():
+    load_library()
+    return _calls
 
 
 def tm_last_error() -> str:
@@ -308,31 +319,12 @@ def tm_group_experts(experts) -> ExpertGroup:
 
 def tm_gemm_w4a16_grouped(X, group: ExpertGroup, offsets, Y, stream=None):
     """Rows offsets[e]..offsets[e+1] of X [R,K] times expert e -> the same rows of Y [R,N]; offsets int32 on the device."""
-    import torch
-    R = X.shape[0]
-    if X.dim() != 2 or X.shape[1] != group.K or tuple(Y.shape) != (R, group.N) or offsets.numel() != len(group.experts) + 1:
-        raise ValueError("X/Y/offsets shapes do not match the expert group")
-    if R == 0:
-        return Y
-    _check(load_library().tm_gemm_w4a16_grouped(_dev_ptr(X, torch.float16, "X"), group.handle,
-                                                _dev_ptr(offsets, torch.int32, "offsets"),
-                                                _dev_ptr(Y, torch.float16, "Y"), R, _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm_grouped(X, group, offsets, Y, TM_ACT_NONE, stream)
 
 
 def tm_gemm_w4a16_grouped_act(X, group: ExpertGroup, offsets, Y, act: int = 1, stream=None):
     """The grouped call with silu(gate)*up fused: experts packed by tm_pack_w4_gate_up, Y [R, N/2]."""
-    import torch
-    R = X.shape[0]
-    n_out = group.N // 2 if act == 1 else group.N
-    if X.dim() != 2 or X.shape[1] != group.K or tuple(Y.shape) != (R, n_out) or offsets.numel() != len(group.experts) + 1:
-        raise ValueError("X/Y/offsets shapes do not match the expert group")
-    if R == 0:
-        return Y
-    _check(load_library().tm_gemm_w4a16_grouped_act(_dev_ptr(X, torch.float16, "X"), group.handle,
-                                                    _dev_ptr(offsets, torch.int32, "offsets"),
-                                                    _dev_ptr(Y, torch.float16, "Y"), R, int(act), _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm_grouped(X, group, offsets, Y, act, stream)
 
 
 def tm_get_grouped_plan(group: ExpertGroup, total_rows: int):
@@ -343,28 +335,12 @@ def tm_get_grouped_plan(group: ExpertGroup, total_rows: int):
 
 def tm_gemm_w4a16(X, packed: PackedW4, Y, stream=None):
     """Y[M,N] = X[M,K] * dequant(packed); X, Y float16 device tensors; enqueued on the current stream."""
-    import torch
-    M = X.shape[0]
-    if X.dim() != 2 or X.shape[1] != packed.K or tuple(Y.shape) != (M, packed.N):
-        raise ValueError("X/Y shapes do not match the packed weight")
-    if M == 0:
-        return Y
-    _check(load_library().tm_gemm_w4a16(_dev_ptr(X, torch.float16, "X"), packed.handle,
-                                        _dev_ptr(Y, torch.float16, "Y"), M, _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm(X, packed, Y, stream)
 
 
 def tm_gemm_w4a16_static(X, packed: PackedW4, Y, stream=None):
     """tm_gemm_w4a16 through the library's fixed scratch array: the call allocates nothing (see include/tm_w4.h)."""
-    import torch
-    M = X.shape[0]
-    if X.dim() != 2 or X.shape[1] != packed.K or tuple(Y.shape) != (M, packed.N):
-        raise ValueError("X/Y shapes do not match the packed weight")
-    if M == 0:
-        return Y
-    _check(load_library().tm_gemm_w4a16_static(_dev_ptr(X, torch.float16, "X"), packed.handle,
-                                               _dev_ptr(Y, torch.float16, "Y"), M, _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm_static(X, packed, Y, stream)
 
 
 TM_ACT_NONE, TM_ACT_SILU_MUL = 0, 1
@@ -373,19 +349,7 @@ TM_ACT_NONE, TM_ACT_SILU_MUL = 0, 1
 def tm_gemm_w4a16_ex(X, packed: PackedW4, Y, bias=None, residual=None, act: int = TM_ACT_NONE, stream=None):
     """Y = fp16(act(X * dequant(packed) + bias) + residual); with TM_ACT_SILU_MUL (handles of tm_pack_w4_gate_up) Y and
     residual are [M, N/2].  All float16 device tensors."""
-    import torch
-    M = X.shape[0]
-    n_out = packed.N // 2 if act == TM_ACT_SILU_MUL else packed.N
-    if X.dim() != 2 or X.shape[1] != packed.K or tuple(Y.shape) != (M, n_out) or \
-            (bias is not None and tuple(bias.shape) != (packed.N,)) or (residual is not None and tuple(residual.shape) != (M, n_out)):
-        raise ValueError("X / Y / bias / residual shapes do not match the packed weight")
-    if M == 0:
-        return Y
-    epi = TmEpilogue(None if bias is None else _dev_ptr(bias, torch.float16, "bias"),
-                     None if residual is None else _dev_ptr(residual, torch.float16, "residual"), int(act))
-    _check(load_library().tm_gemm_w4a16_ex(_dev_ptr(X, torch.float16, "X"), packed.handle, _dev_ptr(Y, torch.float16, "Y"), M,
-                                           ctypes.byref(epi), _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm_ex(X, packed, Y, bias, residual, act, stream)
 
 
 def tm_pack_w4_gate_up(qweight, scales, zeros, K: int, N: int, group: int, stream=None) -> PackedW4:
@@ -403,17 +367,7 @@ def tm_pack_w4_gate_up(qweight, scales, zeros, K: int, N: int, group: int, strea
 
 
 def tm_gemm_w4a16_ws(X, packed: PackedW4, Y, workspace, stream=None):
-    import torch
-    M = X.shape[0]
-    if X.dim() != 2 or X.shape[1] != packed.K or tuple(Y.shape) != (M, packed.N):
-        raise ValueError("X/Y shapes do not match the packed weight")
-    if M == 0:
-        return Y
-    _check(load_library().tm_gemm_w4a16_ws(_dev_ptr(X, torch.float16, "X"), packed.handle,
-                                           _dev_ptr(Y, torch.float16, "Y"), M,
-                                           _dev_ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
-                                           _stream_ptr(stream)))
-    return Y
+    return (_calls or _native()).gemm_ws(X, packed, Y, workspace, stream)
 
 
 def tm_reset_workspace(workspace=None, stream=None):
@@ -556,37 +510,18 @@ def tm_kv_create(batch: int, kv_heads: int, capacity: int, bits: int = 8) -> KvC
 
 def tm_kv_append(cache: KvCache, K_new, V_new, positions, stream=None):
     """K_new, V_new float16 [batch, count, kv_heads, 128]; positions int32 [batch] (device)."""
-    import torch
-    if K_new.dim() != 4 or tuple(K_new.shape) != tuple(V_new.shape) or K_new.shape[0] != cache.batch or \
-            K_new.shape[2] != cache.kv_heads or K_new.shape[3] != 128 or positions.numel() != cache.batch:
-        raise ValueError("K_new / V_new / positions shapes do not match the cache")
-    _check(load_library().tm_kv_append(cache.handle, _dev_ptr(K_new, torch.float16, "K_new"),
-                                       _dev_ptr(V_new, torch.float16, "V_new"), _dev_ptr(positions, torch.int32, "positions"),
-                                       K_new.shape[1], _stream_ptr(stream)))
+    return (_calls or _native()).kv_append(cache, K_new, V_new, positions, stream)
 
 
 def tm_attn_decode(Q, cache: KvCache, lens, O, scale: float, max_len: int = 0, stream=None):
     """Q, O float16 [batch, q_heads, 128]; lens int32 [batch] (device)."""
-    import torch
-    if Q.dim() != 3 or Q.shape[0] != cache.batch or Q.shape[2] != 128 or tuple(O.shape) != tuple(Q.shape) or \
-            lens.numel() != cache.batch:
-        raise ValueError("Q / O / lens shapes do not match the cache")
-    _check(load_library().tm_attn_decode(_dev_ptr(Q, torch.float16, "Q"), cache.handle, _dev_ptr(lens, torch.int32, "lens"),
-                                         _dev_ptr(O, torch.float16, "O"), Q.shape[1], float(scale), int(max_len),
-                                         _stream_ptr(stream)))
-    return O
+    return (_calls or _native()).attn_decode(Q, cache, lens, O, scale, max_len, stream)
 
 
 def tm_attn_prefill(Q, cache: KvCache, positions, O, scale: float, counts=None, stream=None):
     """Causal attention of a chunk of prompt tokens over the cache: Q, O fp16 [batch][count][q_heads][128] device tensors,
     positions int32 [batch], counts int32 [batch] or None (see include/tm_attn.h)."""
-    import torch
-    if Q.dim() != 4 or Q.shape[3] != 128 or tuple(O.shape) != tuple(Q.shape):
-        raise ValueError("Q and O must be [batch][count][q_heads][128]")
-    cp = None if counts is None else _dev_ptr(counts, torch.int32, "counts")
-    _check(load_library().tm_attn_prefill(_dev_ptr(Q, torch.float16, "Q"), cache.handle, _dev_ptr(positions, torch.int32, "positions"),
-                                          cp, Q.shape[1], _dev_ptr(O, torch.float16, "O"), Q.shape[2], scale, _stream_ptr(stream)))
-    return O
+    return (_calls or _native()).attn_prefill(Q, cache, positions, O, scale, counts, stream)
 
 
 def tm_kv_raw(cache: KvCache):

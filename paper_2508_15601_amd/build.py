@@ -1,14 +1,17 @@
-"""Build libtm_w4.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Build libtm_w4.so and the native half of the Python binding (tm_calls.so) in-tree with hipcc for gfx950
+(cross-compiles without a GPU)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libtm_w4.so")
+CALLS = os.path.join(PKG, "tm_calls.so")
 SOURCES = ["tm_w4_api.hip", "tm_w4_pack.hip", "tm_w4_skinny.hip", "tm_w4_stream.hip", "tm_w4_stream_grouped.hip", "tm_w4_streamx.hip", "tm_w4_streamx64.hip", "tm_w4_skinny_w8.hip", "tm_w4_skinny_f8.hip", "tm_w4_tile_small.hip", "tm_w4_tile_large.hip", "tm_w4_tile32.hip",
            "tm_w4_tile_kgroup.hip", "tm_w4_tile_grouped.hip", "tm_w4_tile_w8.hip", "tm_attn.hip"]
 # per-file extra flags (see the header comment of each file)
@@ -21,8 +24,8 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hi
          "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
-    """Compile every translation unit and link the shared library.  Always rebuilds."""
+def build(verbose: bool = False, jobs: int = 8) -> str:
+    """Compile every translation unit and link the two shared objects.  Always rebuilds."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     out = LIB
     objdir = os.path.join(PKG, "_build")
@@ -43,7 +46,26 @@ def build(verbose: bool = False, jobs: int = 4) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_calls(hipcc, verbose)
     return out
+
+
+def build_calls(hipcc: str, verbose: bool = False) -> str:
+    """The binding's native entry points: host code against PyTorch's headers, linked to the library beside it."""
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    cmd = [hipcc, "-x", "c++", os.path.join(CSRC, "tm_calls.cpp"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(troot, "include"),
+           "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc))), "include"), "-o", CALLS, "-L", PKG, "-l:libtm_w4.so", "-Wl,-rpath,$ORIGIN",
+           "-L", os.path.join(troot, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    done = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if done.returncode != 0:
+        raise RuntimeError(f"hipcc failed on tm_calls.cpp:\n{done.stdout}")
+    return CALLS
 
 
 def _drain(procs):

@@ -1,0 +1,48 @@
+"""The native entry points of the binding refuse arguments as the binding promises: TypeError for anything but a device
+tensor of the right type, ValueError for shapes and freed handles.  Runs without a GPU: every case ends before a launch."""
+import types
+
+import pytest
+import torch
+
+import paper_2508_15601_amd as tm
+
+
+def half(*shape):
+    return torch.zeros(shape, dtype=torch.float16)
+
+
+PACKED = types.SimpleNamespace(_h=0, K=256, N=32)
+GROUP = types.SimpleNamespace(_h=0, K=256, N=32, experts=[None, None])
+CACHE = types.SimpleNamespace(_h=0, batch=2, kv_heads=4)
+OFF = torch.zeros(3, dtype=torch.int32)
+
+
+@pytest.mark.parametrize("call, error", [
+    (lambda: tm.tm_gemm_w4a16([0.0], PACKED, half(1, 32)), TypeError),
+    (lambda: tm.tm_gemm_w4a16(half(1, 256), PACKED, half(1, 32)), TypeError),          # host tensors
+    (lambda: tm.tm_gemm_w4a16(half(256), PACKED, half(1, 32)), ValueError),
+    (lambda: tm.tm_gemm_w4a16(half(1, 128), PACKED, half(1, 32)), ValueError),
+    (lambda: tm.tm_gemm_w4a16(half(2, 256), PACKED, half(1, 32)), ValueError),
+    (lambda: tm.tm_gemm_w4a16_static(half(2, 256), PACKED, half(2, 16)), ValueError),
+    (lambda: tm.tm_gemm_w4a16_ws(half(2, 256), PACKED, half(1, 32), None), ValueError),
+    (lambda: tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 32), act=1), ValueError),
+    (lambda: tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 32), bias=half(16)), ValueError),
+    (lambda: tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 32), residual=half(1, 32)), ValueError),
+    (lambda: tm.tm_gemm_w4a16_grouped(half(2, 256), GROUP, OFF[:2], half(2, 32)), ValueError),
+    (lambda: tm.tm_gemm_w4a16_grouped_act(half(2, 256), GROUP, OFF, half(2, 32)), ValueError),
+    (lambda: tm.tm_kv_append(CACHE, half(2, 1, 4, 64), half(2, 1, 4, 64), OFF[:2]), ValueError),
+    (lambda: tm.tm_kv_append(CACHE, half(2, 1, 4, 128), half(2, 1, 4, 128), OFF), ValueError),
+    (lambda: tm.tm_kv_append(CACHE, half(2, 1, 4, 128), half(2, 1, 4, 128), OFF[:2]), ValueError),      # freed cache
+    (lambda: tm.tm_attn_decode(half(2, 8, 128), CACHE, OFF[:2], half(2, 4, 128), 1.0), ValueError),
+    (lambda: tm.tm_attn_prefill(half(2, 8, 128), CACHE, OFF[:2], half(2, 8, 128), 1.0), ValueError),
+])
+def test_arguments_are_refused(call, error):
+    with pytest.raises(error):
+        call()
+
+
+@pytest.mark.parametrize("empty", [lambda: tm.tm_gemm_w4a16(half(0, 256), PACKED, half(0, 32)),
+                                   lambda: tm.tm_gemm_w4a16_ex(half(0, 256), PACKED, half(0, 32))])
+def test_no_rows_is_a_no_op_that_returns_the_output(empty):
+    assert tuple(empty().shape) == (0, 32)
