@@ -88,9 +88,9 @@ TM_API int tm_attn_decode(const uint16_t* Q, const tm_kv_cache* cache, const int
  * stream).  counts (int32 [batch], device, or NULL = every sequence has `count` tokens) gives the query tokens each
  * sequence really has, so that prompts of different lengths share one call: rows i >= counts[b] of O, and rows whose
  * position falls outside [0, capacity), are left untouched.  q_heads and scale as for tm_attn_decode; 1 <= count <= 65535
- * * (16 / min(G, 16)), G = q_heads / kv_heads.  One CTA takes 16 / min(G, 16) consecutive tokens of one KV head and streams
- * the cache up to the last of them; the context is not split, so a short chunk far into a long context is served by few
- * CTAs (use tm_attn_decode per token there).  Never allocates, uses no workspace, results are bit-identical from run to
+ * * (16 / min(G, 16)), G = q_heads / kv_heads.  One CTA takes 128 or 256 (token, query head) rows of one KV head where
+ * they fill the chip, 16 / min(G, 16) consecutive tokens otherwise, and streams the cache up to the last of them; the
+ * context is not split across CTAs, so a short chunk far into a long context is served by few CTAs.  Never allocates, uses no workspace, results are bit-identical from run to
  * run.
  */
 TM_API int tm_attn_prefill(const uint16_t* Q, const tm_kv_cache* cache, const int32_t* positions, const int32_t* counts,

@@ -708,7 +708,8 @@ __device__ __forceinline__ void store_out4(uint16_t* O, int b, int q_heads, int 
 constexpr int kPartialFloats = 32 + kHeadDim * 16;
 constexpr int kMergeHere = 8;            // splits the last-arriving CTA merges itself (all their loads in flight at once)
 
-// PREFILL: the same kernel over a chunk of prompt tokens (paper Sec. 3.3: one attention pipeline for both phases).  The 16
+// PREFILL: the same kernel over a short chunk of prompt tokens, or one of few heads (paper Sec. 3.3: one attention pipeline for
+// both phases; chunks that fill the chip with 128- or 256-row CTAs run on tm_attn_prefill.hip).  The 16
 // query columns of a CTA are then 16 / G consecutive tokens x the G query heads of the KV head (column c = token c / G,
 // head c % G), blockIdx.z counts such token groups instead of context splits, `lens` holds the cache position of every
 // sequence's first query token, and each column attends causally over the cache up to its own token: the length that
@@ -1105,8 +1106,10 @@ hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int3
 }
 
 hipError_t launch_attn_prefill(const AttnCache& kv, const uint16_t* Q, const int32_t* positions, const int32_t* counts,
-                               int count, uint16_t* O, int q_heads, float scale, hipStream_t stream)
+                               int count, uint16_t* O, int q_heads, float scale, int num_cu, hipStream_t stream)
 {
+    const int rows = attn_prefill_rows(kv, count, q_heads, num_cu);
+    if (rows) return launch_attn_prefill_rows(rows, kv, Q, positions, counts, count, O, q_heads, scale, stream);
     const int group = q_heads / kv.heads;
     const float scale_log2e = scale * 1.4426950408889634f;
     for (int head0 = 0; head0 < group; head0 += 16) {        // one pass per sixteen query heads of a group, as at decode

@@ -45,6 +45,7 @@ struct DeviceState {
     bool supported = false;
     void* workspace = nullptr;
     void* xperm = nullptr;     // kXpermBytes, allocated with the first activation-order handle
+    bool attn_ready = false;   // LDS limits of the prompt attention kernels raised, with the first cache
     void* static_ws = nullptr; // this device's copy of the static scratch array, resolved at the first static call
     int num_cu = 256;
 };
@@ -1579,6 +1580,17 @@ tm_kv_cache* tm_kv_create(int batch, int kv_heads, int capacity, int bits)
     }
     int dev;
     if (check_device(&dev) != TM_OK) return nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        if (!g_dev[dev].attn_ready) {
+            const hipError_t e = attn_prefill_setup();
+            if (e != hipSuccess) {
+                fail_hip(e, "attention set-up");
+                return nullptr;
+            }
+            g_dev[dev].attn_ready = true;
+        }
+    }
     tm_kv_cache* c = new (std::nothrow) tm_kv_cache();
     if (!c) {
         fail(TM_ENOMEM, "host allocation failed");
@@ -1684,7 +1696,8 @@ int tm_attn_prefill(const uint16_t* Q, const tm_kv_cache* cache, const int32_t* 
     int rc = check_device(&dev);
     if (rc != TM_OK) return rc;
     if (dev != cache->device) return fail(TM_EINVAL, "cache lives on device %d, current device is %d", cache->device, dev);
-    hipError_t e = launch_attn_prefill(cache->kv, Q, positions, counts, count, O, q_heads, scale, (hipStream_t)stream);
+    hipError_t e = launch_attn_prefill(cache->kv, Q, positions, counts, count, O, q_heads, scale, g_dev[dev].num_cu,
+                                       (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "attention launch");
     return TM_OK;
 }

@@ -100,7 +100,11 @@ hipError_t launch_kv_append(const AttnCache& kv, const uint16_t* Kn, const uint1
 hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int32_t* lens, uint16_t* O, int q_heads,
                               float scale, int max_len, int num_cu, hipStream_t stream);
 hipError_t launch_attn_prefill(const AttnCache& kv, const uint16_t* Q, const int32_t* positions, const int32_t* counts,
-                               int count, uint16_t* O, int q_heads, float scale, hipStream_t stream);
+                               int count, uint16_t* O, int q_heads, float scale, int num_cu, hipStream_t stream);
+hipError_t attn_prefill_setup();                                       // once per device, outside any capture
+int attn_prefill_rows(const AttnCache& kv, int count, int q_heads, int num_cu);  // rows per CTA, 0: the 16-column kernel
+hipError_t launch_attn_prefill_rows(int rows, const AttnCache& kv, const uint16_t* Q, const int32_t* positions, const int32_t* counts,
+                                    int count, uint16_t* O, int q_heads, float scale, hipStream_t stream);
 hipError_t launch_skinny(const GemmParams& p, const Plan& plan, int group, hipStream_t stream);
 hipError_t launch_stream(const GemmParams& p, const Plan& plan, int group, hipStream_t stream);
 hipError_t stream_setup();                                             // once per device, outside any capture

@@ -401,6 +401,61 @@ def test_attn_prefill_long_prompt_sampled(tm, bits):
     cache.close()
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,Hkv,G,cap,positions,n", [
+    (32, 16, 3, 128, [0, 5, 58, -20, 100], 70),      # 256-row CTAs: two stages, ragged rows, positions outside the cache
+    (8, 16, 3, 128, [0, 5, 58, -20, 100], 70),       # 128-row CTAs (two wave groups along the context)
+    (4, 16, 20, 96, [0, 31, 32, 64], 32),            # more than sixteen query heads per KV head
+    (16, 32, 1, 128, [0, 1, 8], 120),                # one row per token
+    (1, 8, 4, 1344, [331], 1000),                    # many stages after a past that ends inside one, 128 rows
+    (2, 8, 8, 960, [331, 0], 600),                   # the same, 256 rows
+])
+def test_attn_prefill_row_tiles(tm, B, Hkv, G, cap, positions, n, bits):
+    """Chunks with enough rows for 128- and 256-row CTAs: ragged counts, masked edges of runs and stages, tokens of the cache
+    that were never stored (their bytes are set to all ones: not-a-number scales).  Sampled heads against the oracle, within
+    the bounds of the module."""
+    import torch
+    _say(f"attn prefill row tiles B={B} Hkv={Hkv} G={G} cap={cap} n={n} bits={bits}")
+    rng = np.random.default_rng(B * 100 + Hkv + G + bits)
+    pos = np.array([positions[b % len(positions)] for b in range(B)], np.int32)
+    cnt = np.array([n - (7 * b) % n for b in range(B)], np.int32)
+    cache = tm.tm_kv_create(B, Hkv, cap, bits)
+    cbytes = B * Hkv * cache.capacity * 128 * bits // 8
+    tm.tm_kv_upload(cache, np.full(cbytes, 255, np.uint8), np.full(cbytes, 255, np.uint8),
+                    np.full(B * Hkv * cache.capacity * 2, 0xFFFFFFFF, np.uint32))
+    K, V = (rng.standard_normal((B, Hkv, cap, 128)).astype(np.float16) for _ in range(2))
+    live = np.minimum(np.maximum(pos + cnt, 0), cap)
+    for b0 in range(0, B, 8):                            # sequence by sequence: only the tokens up to its last query row
+        for b in range(b0, min(b0 + 8, B)):
+            at = torch.full((B,), cache.capacity, dtype=torch.int32, device="cuda")      # the others' tokens are dropped
+            at[b] = 0
+            if live[b]:
+                Kn, Vn = (np.zeros((B, live[b], Hkv, 128), np.float16) for _ in range(2))
+                Kn[b], Vn[b] = K[b, :, :live[b]].transpose(1, 0, 2), V[b, :, :live[b]].transpose(1, 0, 2)
+                tm.tm_kv_append(cache, _dev(Kn), _dev(Vn), at)
+    Q = rng.standard_normal((B, n, Hkv * G, 128)).astype(np.float16)
+    outs = []
+    for _ in range(2):
+        O = torch.full((B, n, Hkv * G, 128), float("nan"), dtype=torch.float16, device="cuda")
+        tm.tm_attn_prefill(_dev(Q), cache, _dev(pos), O, 128 ** -0.5, counts=_dev(cnt))
+        torch.cuda.synchronize()
+        outs.append(O.cpu().numpy())
+    assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    for b in sorted({0, 1, B // 2, B - 2, B - 1} & set(range(B))):
+        hk = int(rng.integers(Hkv))
+        heads = slice(hk * G, (hk + 1) * G)
+        kq, vq = oa.kv_quantise(K[b:b + 1, hk:hk + 1], bits), oa.kv_quantise(V[b:b + 1, hk:hk + 1], bits)
+        rows = [i for i in range(cnt[b]) if 0 <= pos[b] + i < cap]
+        for i in {*rows[:3], *rows[-3:], *rows[len(rows) // 2:len(rows) // 2 + 2]}:
+            ref = oa.attn_prefill(Q[b:b + 1, i:i + 1, heads], *kq, *vq, pos[b:b + 1] + i, np.array([1], np.int32), 128 ** -0.5)
+            ok, worst, fro = _close(outs[0][b:b + 1, i:i + 1, heads], ref)
+            assert ok, (b, i, worst, fro)
+        dead = [i for i in range(n) if i not in rows]
+        assert np.isnan(outs[0][b, dead]).all()          # rows past the count or outside the cache are left alone
+        assert not np.isnan(outs[0][b, rows]).any()
+    cache.close()
+
+
 def test_attn_prefill_argument_checks(tm):
     import torch
     cache = tm.tm_kv_create(1, 2, 64, 8)
