@@ -40,65 +40,91 @@ __device__ __forceinline__ float xor_max(float v, int mask) { return fmaxf(v, __
 __device__ __forceinline__ float xor_add(float v, int mask) { return v + __shfl_xor(v, mask); }
 
 // ------------------------------------------------------------------------------------------------ quantise + store
-// One wave per (sequence, new token, KV head); lane l owns dimensions l and l + 64 of the key and of the value.
-__global__ __launch_bounds__(64) void kv_append_kernel(AttnCache kv, const uint16_t* __restrict__ Kn,
-                                                       const uint16_t* __restrict__ Vn,
-                                                       const int32_t* __restrict__ positions, int count)
+// Minimum and maximum over the wave, in every lane: rotations within the rows of sixteen lanes, then swaps between rows.
+__device__ __forceinline__ void wave_min_max(float& mn, float& mx)
 {
-    const int lane = threadIdx.x;
+    auto fold = [&](auto CTRL) {
+        constexpr int ctrl = decltype(CTRL)::value;        // row_ror by 8, 4, 2, 1
+        const float a = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, mn), ctrl, 0xf, 0xf, true));
+        const float b = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, mx), ctrl, 0xf, 0xf, true));
+        mn = fminf(mn, a);
+        mx = fmaxf(mx, b);
+    };
+    fold(std::integral_constant<int, 0x128>{});
+    fold(std::integral_constant<int, 0x124>{});
+    fold(std::integral_constant<int, 0x122>{});
+    fold(std::integral_constant<int, 0x121>{});
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto pair = [](auto r, auto f) { return f(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])); };
+    auto lo = [](float x, float y) { return fminf(x, y); };
+    auto hi = [](float x, float y) { return fmaxf(x, y); };
+    uint32_t a = __builtin_bit_cast(uint32_t, mn), b = __builtin_bit_cast(uint32_t, mx);
+    mn = pair(__builtin_amdgcn_permlane16_swap(a, a, false, false), lo);
+    mx = pair(__builtin_amdgcn_permlane16_swap(b, b, false, false), hi);
+    a = __builtin_bit_cast(uint32_t, mn), b = __builtin_bit_cast(uint32_t, mx);
+    mn = pair(__builtin_amdgcn_permlane32_swap(a, a, false, false), lo);
+    mx = pair(__builtin_amdgcn_permlane32_swap(b, b, false, false), hi);
+#endif
+}
+
+// The codes of the lane's two values and the vector's scale / zero word.
+template <int BITS>
+__device__ __forceinline__ uint32_t quantise_pair(float x0, float x1, uint32_t& q0, uint32_t& q1)
+{
+    constexpr float top = BITS == 8 ? 255.0f : 15.0f;
+    float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
+    wave_min_max(mn, mx);
+    _Float16 s16 = (_Float16)((mx - mn) / top);
+    float sf = (float)s16;
+    if (!(sf > 0.0f) || __builtin_isinf(sf)) {
+        sf = 1.0f;
+        s16 = (_Float16)1.0f;
+    }
+    const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), top);
+    q0 = (uint32_t)fminf(fmaxf(rintf(x0 / sf) + zf, 0.0f), top);
+    q1 = (uint32_t)fminf(fmaxf(rintf(x1 / sf) + zf, 0.0f), top);
+    return (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, (_Float16)zf) << 16);
+}
+
+// The append of a decoding step (few tokens).  A CTA of two waves per (sequence, new token, KV head): one quantises the
+// key, one the value; lane l owns dimensions l and l + 64.  Such a launch is one chain of dependent latencies, so the vector
+// is requested together with the sequence's position, not after it.
+__global__ __launch_bounds__(128) void kv_append_kernel(AttnCache kv, const uint16_t* __restrict__ Kn,
+                                                        const uint16_t* __restrict__ Vn,
+                                                        const int32_t* __restrict__ positions, int count)
+{
+    const int lane = threadIdx.x & 63, which = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = blockIdx.x % kv.heads;
     const int j = (blockIdx.x / kv.heads) % count;
     const int b = blockIdx.x / (kv.heads * count);
+    const uint16_t* const x = (which ? Vn : Kn) + (((size_t)b * count + j) * kv.heads + h) * kHeadDim;
+    const uint16_t r0 = x[lane], r1 = x[lane + 64];
     const int t = positions[b] + j;
-    if (t < 0 || t >= kv.cap) return;                       // wave-uniform
-    const size_t src = (((size_t)b * count + j) * kv.heads + h) * kHeadDim;
+    if (t < 0 || t >= kv.cap) return;                       // CTA-uniform
     const size_t bh = (size_t)b * kv.heads + h;
+    uint32_t q0, q1;
+    const uint32_t pair = quantise_pair<8>((float)__builtin_bit_cast(_Float16, r0), (float)__builtin_bit_cast(_Float16, r1), q0, q1);
+    const int u = t & 31;
+    uint8_t* const blk = (which ? kv.v : kv.k) + (bh * (kv.cap / 32) + (t >> 5)) * 4096;
+    if (which == 0) {
+        // dimension d -> byte ((i*2 + half)*64 + 16*hh + c)*16 + x, i = u/16, c = u%16, hh = d/32, half = (d%32)/16
+        const int i = u >> 4, c = u & 15;
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        const uint16_t* x = (which ? Vn : Kn) + src;
-        const float x0 = (float)__builtin_bit_cast(_Float16, x[lane]);
-        const float x1 = (float)__builtin_bit_cast(_Float16, x[lane + 64]);
-        float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            mn = fminf(mn, __shfl_xor(mn, m));
-            mx = fmaxf(mx, __shfl_xor(mx, m));
+        for (int k = 0; k < 2; ++k) {
+            const int d = lane + 64 * k;
+            blk[((i * 2 + ((d & 31) >> 4)) * 64 + 16 * (d >> 5) + c) * 16 + (d & 15)] = (uint8_t)(k ? q1 : q0);
         }
-        _Float16 s16 = (_Float16)((mx - mn) / 255.0f);
-        float sf = (float)s16;
-        if (!(sf > 0.0f) || __builtin_isinf(sf)) {
-            sf = 1.0f;
-            s16 = (_Float16)1.0f;
-        }
-        const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), 255.0f);
-        const uint32_t q0 = (uint32_t)fminf(fmaxf(rintf(x0 / sf) + zf, 0.0f), 255.0f);
-        const uint32_t q1 = (uint32_t)fminf(fmaxf(rintf(x1 / sf) + zf, 0.0f), 255.0f);
-        const int u = t & 31;
-        uint8_t* blk = (which ? kv.v : kv.k) + (bh * (kv.cap / 32) + (t >> 5)) * 4096;
-        if (which == 0) {
-            // dimension d -> byte ((j*2 + half)*64 + 16*hh + c)*16 + x, j = u/16, c = u%16, hh = d/32, half = (d%32)/16
-            const int j = u >> 4, c = u & 15;
+    } else {
+        // dimension d = 16*i + c -> byte ((i/2)*64 + 16*hh + c)*16 + (i%2)*8 + e, hh = (u%16)/4, e = u%4 + 4*(u/16)
+        const int hh = (u & 15) >> 2, e = (u & 3) + 4 * (u >> 4);
+        const int c = lane & 15;
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int d = lane + 64 * k;
-                blk[((j * 2 + ((d & 31) >> 4)) * 64 + 16 * (d >> 5) + c) * 16 + (d & 15)] = (uint8_t)(k ? q1 : q0);
-            }
-        } else {
-            // dimension d = 16*i + c -> byte ((i/2)*64 + 16*hh + c)*16 + (i%2)*8 + e, hh = (u%16)/4, e = u%4 + 4*(u/16)
-            const int hh = (u & 15) >> 2, e = (u & 3) + 4 * (u >> 4);
-            const int c = lane & 15;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int i = (lane >> 4) + 4 * k;
-                blk[((i >> 1) * 64 + 16 * hh + c) * 16 + (i & 1) * 8 + e] = (uint8_t)(k ? q1 : q0);
-            }
-        }
-        if (lane == 0) {
-            const _Float16 z16 = (_Float16)zf;
-            kv.sz[(bh * kv.cap + t) * 2 + which] =
-                (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, z16) << 16);
+        for (int k = 0; k < 2; ++k) {
+            const int i = (lane >> 4) + 4 * k;
+            blk[((i >> 1) * 64 + 16 * hh + c) * 16 + (i & 1) * 8 + e] = (uint8_t)(k ? q1 : q0);
         }
     }
+    if (lane == 0) kv.sz[(bh * kv.cap + t) * 2 + which] = pair;
 }
 
 // Prompt-sized appends: one CTA of 256 threads per (KV head, 32-token block touched, sequence).  Sixteen lanes share a
@@ -333,78 +359,58 @@ __global__ __launch_bounds__(256) void kv4_append_block_kernel(AttnCache kv, con
     *vdst = vc;
 }
 
-// 4-bit codes, one new token per sequence (the append of a decoding step): one wave per (sequence, KV head); lane l owns
-// dimensions l and l + 64.  Key codes: the eight lanes of an operand word OR their nibbles together and one of them
-// stores the word.  Value codes: every dimension has its own word, shared with seven other tokens, so each lane replaces
-// one nibble in each of its two words (no other wave of the launch touches this sequence and head).
-__global__ __launch_bounds__(64) void kv4_append_token_kernel(AttnCache kv, const uint16_t* __restrict__ Kn,
-                                                              const uint16_t* __restrict__ Vn,
-                                                              const int32_t* __restrict__ positions)
+// 4-bit codes, one new token per sequence (the append of a decoding step): one wave for the key and one for the value of a
+// (sequence, KV head); lane l owns dimensions l and l + 64.  Key codes: the eight lanes of an operand word OR their nibbles
+// together and one of them stores the word.  Value codes: every dimension has its own word, shared with seven other tokens,
+// so each lane replaces one nibble in each of its two words (no other wave of the launch touches this sequence and head's).
+__global__ __launch_bounds__(128) void kv4_append_token_kernel(AttnCache kv, const uint16_t* __restrict__ Kn,
+                                                               const uint16_t* __restrict__ Vn,
+                                                               const int32_t* __restrict__ positions)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, which = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = blockIdx.x % kv.heads, b = blockIdx.x / kv.heads;
-    const int t = positions[b];
-    if (t < 0 || t >= kv.cap) return;                       // wave-uniform
     const size_t bh = (size_t)b * kv.heads + h;
-    const size_t src = bh * kHeadDim;
+    const uint16_t* const x = (which ? Vn : Kn) + bh * kHeadDim;
+    const uint16_t r0 = x[lane], r1 = x[lane + 64];
+    const int t = positions[b];
+    if (t < 0 || t >= kv.cap) return;                       // CTA-uniform
     const int u = t & 31;
     const size_t blk = (bh * (kv.cap / 32) + (t >> 5)) * 512;      // in words
+    // dimension d = 16*i + c: word ((i/4)*64 + 16*hh + c)*4 + i%4, hh = (u%16)/4; this token is operand element
+    // e = u%4 + 4*(u/16) of the word.  The words are requested before the arithmetic.
+    const int ve = (u & 3) + 4 * (u >> 4), vsh = 4 * ((ve >> 1) + 4 * (ve & 1));
+    uint32_t* vp[2];
+    uint32_t old[2] = {0u, 0u};
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        const uint16_t* x = (which ? Vn : Kn) + src;
-        const float x0 = (float)__builtin_bit_cast(_Float16, x[lane]);
-        const float x1 = (float)__builtin_bit_cast(_Float16, x[lane + 64]);
-        float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            mn = fminf(mn, __shfl_xor(mn, m));
-            mx = fmaxf(mx, __shfl_xor(mx, m));
-        }
-        _Float16 s16 = (_Float16)((mx - mn) / 15.0f);
-        float sf = (float)s16;
-        if (!(sf > 0.0f) || __builtin_isinf(sf)) {
-            sf = 1.0f;
-            s16 = (_Float16)1.0f;
-        }
-        const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), 15.0f);
-        const uint32_t q0 = (uint32_t)fminf(fmaxf(rintf(x0 / sf) + zf, 0.0f), 15.0f);
-        const uint32_t q1 = (uint32_t)fminf(fmaxf(rintf(x1 / sf) + zf, 0.0f), 15.0f);
-        if (which == 0) {
-            // dimension d = 32*hh + 8*tt + e: word ((u/16)*64 + 16*hh + u%16)*4 + tt, nibble e/2 + 4*(e % 2)
-            const int e = lane & 7;
-            const int sh = 4 * ((e >> 1) + 4 * (e & 1));
-            uint32_t w0 = q0 << sh, w1 = q1 << sh;
-#pragma unroll
-            for (int m = 1; m < 8; m <<= 1) {
-                w0 |= (uint32_t)__shfl_xor((int)w0, m);
-                w1 |= (uint32_t)__shfl_xor((int)w1, m);
-            }
-            if (e == 0) {
-                uint32_t* kw = reinterpret_cast<uint32_t*>(kv.k) + blk;
-                const int d = lane;                          // and d + 64: two more 32-dimension groups up
-                const int word = ((u >> 4) * 64 + 16 * (d >> 5) + (u & 15)) * 4 + ((d & 31) >> 3);
-                kw[word] = w0;
-                kw[word + 2 * 16 * 4] = w1;
-            }
-        } else {
-            // dimension d = 16*i + c: word ((i/4)*64 + 16*hh + c)*4 + i%4, hh = (u%16)/4; this token is operand element
-            // e = u%4 + 4*(u/16) of the word
-            const int e = (u & 3) + 4 * (u >> 4), hh = (u & 15) >> 2;
-            const int sh = 4 * ((e >> 1) + 4 * (e & 1));
-            uint32_t* vw = reinterpret_cast<uint32_t*>(kv.v) + blk;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int d = lane + 64 * k, i = d >> 4;
-                uint32_t* wp = vw + ((i >> 2) * 64 + 16 * hh + (d & 15)) * 4 + (i & 3);
-                *wp = (*wp & ~(0xfu << sh)) | ((k ? q1 : q0) << sh);
-            }
-        }
-        if (lane == 0) {
-            const _Float16 z16 = (_Float16)zf;
-            kv.sz[(bh * kv.cap + t) * 2 + which] =
-                (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, z16) << 16);
-        }
+    for (int k = 0; k < 2; ++k) {
+        const int d = lane + 64 * k, i = d >> 4;
+        vp[k] = reinterpret_cast<uint32_t*>(kv.v) + blk + ((i >> 2) * 64 + 16 * ((u & 15) >> 2) + (d & 15)) * 4 + (i & 3);
+        if (which) old[k] = *vp[k];
     }
+    uint32_t q0, q1;
+    const uint32_t pair = quantise_pair<4>((float)__builtin_bit_cast(_Float16, r0), (float)__builtin_bit_cast(_Float16, r1), q0, q1);
+    if (which == 0) {
+        // dimension d = 32*hh + 8*tt + e: word ((u/16)*64 + 16*hh + u%16)*4 + tt, nibble e/2 + 4*(e % 2)
+        const int e = lane & 7;
+        const int sh = 4 * ((e >> 1) + 4 * (e & 1));
+        uint32_t w0 = q0 << sh, w1 = q1 << sh;
+#pragma unroll
+        for (int m = 1; m < 8; m <<= 1) {
+            w0 |= (uint32_t)__shfl_xor((int)w0, m);
+            w1 |= (uint32_t)__shfl_xor((int)w1, m);
+        }
+        if (e == 0) {
+            uint32_t* kw = reinterpret_cast<uint32_t*>(kv.k) + blk;
+            const int d = lane;                              // and d + 64: two more 32-dimension groups up
+            const int word = ((u >> 4) * 64 + 16 * (d >> 5) + (u & 15)) * 4 + ((d & 31) >> 3);
+            kw[word] = w0;
+            kw[word + 2 * 16 * 4] = w1;
+        }
+    } else {
+        *vp[0] = (old[0] & ~(0xfu << vsh)) | (q0 << vsh);
+        *vp[1] = (old[1] & ~(0xfu << vsh)) | (q1 << vsh);
+    }
+    if (lane == 0) kv.sz[(bh * kv.cap + t) * 2 + which] = pair;
 }
 
 // ------------------------------------------------------------------------------------------------ decode attention
@@ -1023,12 +1029,12 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnCache kv, uint16_t*
 hipError_t launch_kv_append(const AttnCache& kv, const uint16_t* Kn, const uint16_t* Vn, const int32_t* positions,
                             int count, hipStream_t stream)
 {
-    const long waves = (long)kv.batch * count * kv.heads;
-    if (waves <= 0 || waves > 0x7fffffffL) return hipErrorInvalidValue;
+    const long tokens = (long)kv.batch * count * kv.heads;
+    if (tokens <= 0 || tokens > 0x7fffffffL) return hipErrorInvalidValue;
     if (kv.bits == 4) {
         if (kv.heads > 65535 || kv.batch > 65535 || ((((uintptr_t)Kn | (uintptr_t)Vn) & 15))) return hipErrorInvalidValue;
         if (count == 1) {
-            hipLaunchKernelGGL(kv4_append_token_kernel, dim3((unsigned)waves), dim3(64), 0, stream, kv, Kn, Vn, positions);
+            hipLaunchKernelGGL(kv4_append_token_kernel, dim3((unsigned)tokens), dim3(128), 0, stream, kv, Kn, Vn, positions);
             return hipGetLastError();
         }
         const unsigned blocks = (unsigned)((count + 31) / 32 + 1);
@@ -1043,7 +1049,7 @@ hipError_t launch_kv_append(const AttnCache& kv, const uint16_t* Kn, const uint1
                            positions, count);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)waves), dim3(64), 0, stream, kv, Kn, Vn, positions, count);
+    hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)tokens), dim3(128), 0, stream, kv, Kn, Vn, positions, count);
     return hipGetLastError();
 }
 
