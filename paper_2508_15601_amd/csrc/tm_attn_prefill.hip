@@ -393,18 +393,26 @@ hipError_t attn_prefill_setup()
 
 // Rows per CTA for a chunk of `count` tokens: 256 or 128 here, 0 = the 16-column kernel.  The context is known on the device
 // only, so the rule compares what one token of it costs in each form: rounds of CTAs (512 of the 16-column form fit the
-// chip, 256 of these) times the measured time of a round relative to a round of 16-column CTAs.  2.7 and 4.05 are the values
-// with which none of 240 random launches (16 ... 8192 tokens, 0 ... 16384 before them, 1 ... 32 KV heads, batch 1 ... 8) ran slower
-// than the 16-column form; they average 1.27 times its speed there, within 1.5 % of the best form of each.
+// chip, 256 of these) times the time of a round relative to a round of 16-column CTAs.  What the host does know is the
+// capacity.  Where that is little more than the chunk, the CTAs of a launch attend over anything between nothing and all of it:
+// further rounds fill up evenly, but a launch of one round lasts as long as its longest CTA, up to twice the average (less in
+// short chunks, where fixed costs count).  Where the capacity is much larger the CTAs are taken to be alike and rounds to be whole.
+// With 2.4 and 3.85 no launch of 240 random ones (16 ... 8192 tokens, 0 ... 16384 before them, 1 ... 32 KV heads, batch 1 ... 8) ran
+// slower than in the 16-column form; they average 1.28 times its speed, within 1 % of the best form of each.
 int attn_prefill_rows(const AttnCache& kv, int count, int q_heads, int num_cu)
 {
     const long bh = (long)kv.batch * kv.heads;
     const int group = q_heads / kv.heads, gw = group < 16 ? group : 16;
     const long rows = (long)count * group, groups = (count + 16 / gw - 1) / (16 / gw) * ((group + 15) / 16);
-    auto rounds = [](long ctas, int at_once) { return ctas > at_once ? (double)ctas / at_once : 1.0; };
-    const double t16 = rounds(bh * groups, 2 * num_cu);
-    const double t128 = 2.7 * rounds(bh * ((rows + 127) / 128), num_cu);
-    const double t256 = 4.05 * rounds(bh * ((rows + 255) / 256), num_cu);
+    const double longest = count < kv.cap ? kv.cap / (kv.cap - 0.5 * count) : 2.0;      // over the average, if the cache fills up
+    auto rounds = [&](long ctas) {
+        if (ctas <= num_cu) return 1.0 + (longest - 1.0) * (count < 1024 ? count / 1024.0 : 1.0);
+        const double r = (double)ctas / num_cu, whole = (double)((ctas + num_cu - 1) / num_cu);
+        return r + (whole - r) * (2.0 - longest);
+    };
+    const double t16 = bh * groups > 2 * num_cu ? (double)(bh * groups) / (2 * num_cu) : 1.0;
+    const double t128 = 2.4 * rounds(bh * ((rows + 127) / 128));
+    const double t256 = 3.85 * rounds(bh * ((rows + 255) / 256));
     if (t16 <= t128 && t16 <= t256) return 0;
     return t128 < t256 ? 128 : 256;
 }
