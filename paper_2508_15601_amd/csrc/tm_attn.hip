@@ -461,243 +461,203 @@ __device__ __forceinline__ void load_block(BlockRegs& r, uint32_t* sz_slot, cons
 }
 
 // Running state of one wave (per query head m = lane % 16; m_run is equal in the four lanes that share an m, l_run and
-// corr are per-lane partial sums over the lane's own tokens).
+// corr are per-lane partial sums over the lane's own tokens).  m_run is the reference the exponents are taken against: the
+// largest score up to a factor of 2^kSlack.  It moves only when a score exceeds it by more than that, so a block normally
+// needs no exchange between lanes and no rescaling: the shuffles of a running maximum were the longest part of the chain of
+// dependent instructions that two waves per SIMD cannot hide.  Probabilities of at most 2^kSlack times a scale fit fp16.
 struct SoftmaxState {
     float m_run, l_run, corr;
 };
+template <int BITS>
+constexpr float kSlack = BITS == 8 ? 6.0f : 2.0f;      // 2^6 * (2 * 65504 / 255), 2^2 * (2 * 65504 / 15) < 65504
 
-// Thirty-two tokens (a whole 8-bit block, or half `sb` of a 4-bit block) starting at token t0.  qsum = sum of the
-// query's 128 values, qbias = sum of the conversion bias of each code position times the query value it meets.
-template <int BITS, bool MASKED>
-__device__ __forceinline__ void process_tokens(const BlockRegs& r, int sb, const uint32_t* sz_slot, const f16x8 (&qf)[4],
-                                               float qsum, const f32x4& neg_qbias, const Magic& mg, int t0, int len, int lane,
-                                               SoftmaxState& st, f32x4 (&acc)[8])
-{
-    const int h = lane >> 4;
-    const int rem = len - t0 - 4 * h;          // slot (j, rr) of this lane is a live token iff 16*j + rr < rem
-    // S^T for the two 16-token tiles: rows = tokens, columns = query heads
-    float s[2][4];
-    uint32_t vw[2][4];                         // (scale, zero-point) of the slot's value row; 0 for a dead token
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        // the accumulator starts at minus the bias term: sum_d (bias_d + q_d) Q_d - sum_d bias_d Q_d = sum_d q_d Q_d
-        f32x4 d;
-        if constexpr (BITS == 8) {
-            d = mfma16x16x32(biased8_w8(r.k[j][0].x, r.k[j][0].y), qf[0], neg_qbias);
-            d = mfma16x16x32(biased8_w8(r.k[j][0].z, r.k[j][0].w), qf[1], d);
-            d = mfma16x16x32(biased8_w8(r.k[j][1].x, r.k[j][1].y), qf[2], d);
-            d = mfma16x16x32(biased8_w8(r.k[j][1].z, r.k[j][1].w), qf[3], d);
-        } else {
-            const u32x4 w = r.k[sb][j];
-            d = mfma16x16x32(biased8(w.x, mg), qf[0], neg_qbias);
-            d = mfma16x16x32(biased8(w.y, mg), qf[1], d);
-            d = mfma16x16x32(biased8(w.z, mg), qf[2], d);
-            d = mfma16x16x32(biased8(w.w, mg), qf[3], d);
-        }
-        // (K pair, V pair) of the lane's four tokens 16j + 4h .. +3: eight consecutive words of the slot
-        const u32x4 p0 = *(const u32x4*)(sz_slot + 32 * j + 8 * h);
-        const u32x4 p1 = *(const u32x4*)(sz_slot + 32 * j + 8 * h + 4);
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const bool live = !MASKED || 16 * j + rr < rem;
-            const f16x2 kp = as_f16x2(rr < 2 ? p0[2 * rr] : p1[2 * (rr - 2)]);
-            // a dead token contributes nothing, whatever its pair holds: scale 0 and zero-point 0 for its values
-            vw[j][rr] = live ? (rr < 2 ? p0[2 * rr + 1] : p1[2 * (rr - 2) + 1]) : 0u;
-            // sum_d q_d Q_d  -  z sum_d Q_d  =  sum_d (q_d - z) Q_d ; times the token's scale.  Both steps are written
-            // as fused multiply-adds so that the fp16 pair enters the instruction directly (no separate conversion;
-            // an addend of +0 keeps the second one from being folded into a plain multiply).
-            const float t = __builtin_fmaf(-(float)kp.y, qsum, d[rr]);
-            const float sc = __builtin_fmaf((float)kp.x, t, 0.0f);
-            s[j][rr] = live ? sc : kNegBig;
-        }
-    }
-    // online softmax in base 2 (the query carries scale * log2(e))
-    float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mx = xor_max(xor_max(mx, 16), 32);
-    const float m_new = fmaxf(st.m_run, mx);
-    const float alpha = fast_exp2(st.m_run - m_new);
-    st.m_run = m_new;
-    float psum = 0.f;
-    f16x8 pb;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const float p = fast_exp2(s[j][rr] - m_new);    // 0 for masked tokens
-            psum += p;
-            // probability times the value scale of that token
-            pb[4 * j + rr] = (_Float16)__builtin_fmaf((float)as_f16x2(vw[j][rr]).x, p, 0.0f);
-        }
-    // The correction term must be built from the very fp16 values the matrix core multiplies: the bias is about a
-    // thousand times the payload, so one fp16 ulp of disagreement on a single probability shifts a whole output row by
-    // several per cent.  Left to itself the compiler rounds p * vs once for the operand (fused multiply-and-convert)
-    // and once more, through fp32, for the sum below; the two differ when the fp32 product lands on an fp16 tie.
-    // Pinning the packed operand makes it the only copy.
-    {
-        u32x4 bits = __builtin_bit_cast(u32x4, pb);
-        asm volatile("" : "+v"(bits.x), "+v"(bits.y), "+v"(bits.z), "+v"(bits.w));
-        pb = __builtin_bit_cast(f16x8, bits);
-    }
-    // sum over the lane's tokens of (bias + z) * p': the value code of slot (j, rr) is the k-value 4j + rr of the
-    // second product and carries the bias 1024 - or 64 at positions 2, 3, 6, 7 of a 4-bit word
-    float sum_hi = 0.f, sum_lo = 0.f, zsum = 0.f;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const float pv = (float)pb[4 * j + rr];
-            if (BITS == 8 || rr < 2) sum_hi = __builtin_fmaf(pv, 1.0f, sum_hi);
-            else sum_lo = __builtin_fmaf(pv, 1.0f, sum_lo);
-            zsum = __builtin_fmaf((float)as_f16x2(vw[j][rr]).y, pv, zsum);
-        }
-    const float csum = __builtin_fmaf(1024.0f, sum_hi, __builtin_fmaf(64.0f, sum_lo, zsum));
-    st.l_run = st.l_run * alpha + psum;
-    st.corr = st.corr * alpha + csum;
-    // the running maximum seldom moves after the first blocks: rescale only when some query head needs it
-    if (__any(alpha != 1.0f)) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] *= alpha;
-    }
-    // O^T += V^T P'^T : rows = dimensions (eight 16-row tiles), k = the 32 tokens of the block
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        f16x8 a;
-        if constexpr (BITS == 8) {
-            const u32x4 w = r.v[i >> 1];
-            a = (i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y);
-        } else {
-            a = biased8(r.v[2 * sb + (i >> 2)][i & 3], mg);
-        }
-        acc[i] = mfma16x16x32(a, pb, acc[i]);
-    }
-}
-
-// The same 32 tokens when at most eight query heads share the KV head: the query operand then carries every head twice
-// (column c and c + 8 both hold head c % 8), so both score tiles come out with all 16 columns live, and a lane keeps
-// tile c / 8 only - four scores instead of eight, half the softmax arithmetic.  The probabilities of the other tile's
-// tokens reach the lane through one exchange with lane c ^ 8 before the second product; running sums are per lane over
-// its own tokens and meet at the end (xor 8, 16, 32).
 __device__ __forceinline__ uint32_t swap_half_rows(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);      // row_ror:8 = lane c <-> c ^ 8
 }
 
-template <int BITS, bool MASKED>
-__device__ __forceinline__ void process_tokens_packed(const BlockRegs& r, int sb, const uint32_t* sz_slot,
-                                                      const f16x8 (&qf)[4], float qsum, const f32x4& neg_qbias,
-                                                      const Magic& mg, int t0, int len, int lane, SoftmaxState& st,
-                                                      f32x4 (&acc)[8])
+// Moves the reference to the largest score of every query head so far (mx: the lane's largest new score, not reduced).
+template <bool PACK>
+__device__ __forceinline__ void move_reference(float mx, SoftmaxState& st, f32x4 (&acc)[8])
 {
-    const int h = lane >> 4, jl = (lane >> 3) & 1;           // jl: the 16-token tile this lane keeps
-    const int rem = len - t0 - 4 * h - 16 * jl;              // slot rr of this lane is a live token iff rr < rem
-    f32x4 d[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        if constexpr (BITS == 8) {
-            d[j] = mfma16x16x32(biased8_w8(r.k[j][0].x, r.k[j][0].y), qf[0], neg_qbias);
-            d[j] = mfma16x16x32(biased8_w8(r.k[j][0].z, r.k[j][0].w), qf[1], d[j]);
-            d[j] = mfma16x16x32(biased8_w8(r.k[j][1].x, r.k[j][1].y), qf[2], d[j]);
-            d[j] = mfma16x16x32(biased8_w8(r.k[j][1].z, r.k[j][1].w), qf[3], d[j]);
-        } else {
-            const u32x4 w = r.k[sb][j];
-            d[j] = mfma16x16x32(biased8(w.x, mg), qf[0], neg_qbias);
-            d[j] = mfma16x16x32(biased8(w.y, mg), qf[1], d[j]);
-            d[j] = mfma16x16x32(biased8(w.z, mg), qf[2], d[j]);
-            d[j] = mfma16x16x32(biased8(w.w, mg), qf[3], d[j]);
-        }
-    }
-    // (K pair, V pair) of the lane's four tokens 16*jl + 4h .. +3
-    const u32x4 p0 = *(const u32x4*)(sz_slot + 32 * jl + 8 * h);
-    const u32x4 p1 = *(const u32x4*)(sz_slot + 32 * jl + 8 * h + 4);
-    float s[4];
-    uint32_t vw[4];
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const bool live = !MASKED || rr < rem;
-        const f16x2 kp = as_f16x2(rr < 2 ? p0[2 * rr] : p1[2 * (rr - 2)]);
-        vw[rr] = live ? (rr < 2 ? p0[2 * rr + 1] : p1[2 * (rr - 2) + 1]) : 0u;
-        const float dm = jl ? d[1][rr] : d[0][rr];
-        const float t = __builtin_fmaf(-(float)kp.y, qsum, dm);
-        const float sc = __builtin_fmaf((float)kp.x, t, 0.0f);
-        s[rr] = live ? sc : kNegBig;
-    }
-    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    mx = fmaxf(mx, __builtin_bit_cast(float, swap_half_rows(__builtin_bit_cast(uint32_t, mx))));
+    if constexpr (PACK) mx = fmaxf(mx, __builtin_bit_cast(float, swap_half_rows(__builtin_bit_cast(uint32_t, mx))));
     mx = xor_max(xor_max(mx, 16), 32);
     const float m_new = fmaxf(st.m_run, mx);
     const float alpha = fast_exp2(st.m_run - m_new);
     st.m_run = m_new;
-    float psum = 0.f;
-    _Float16 own[4];
+    st.l_run *= alpha;
+    st.corr *= alpha;
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const float p = fast_exp2(s[rr] - m_new);            // 0 for masked tokens
-        psum += p;
-        own[rr] = (_Float16)__builtin_fmaf((float)as_f16x2(vw[rr]).x, p, 0.0f);
-    }
-    // the lane's four probabilities as two operand words, pinned (the correction below must see the very bits the
-    // matrix core multiplies), then the other tile's four from lane c ^ 8
-    uint32_t o0 = (uint32_t)__builtin_bit_cast(uint16_t, own[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, own[1]) << 16);
-    uint32_t o1 = (uint32_t)__builtin_bit_cast(uint16_t, own[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, own[3]) << 16);
-    asm volatile("" : "+v"(o0), "+v"(o1));
-    const uint32_t x0 = swap_half_rows(o0), x1 = swap_half_rows(o1);
-    u32x4 pbits;
-    pbits.x = jl ? x0 : o0;                                  // k-values 0..3: tile 0, 4..7: tile 1
-    pbits.y = jl ? x1 : o1;
-    pbits.z = jl ? o0 : x0;
-    pbits.w = jl ? o1 : x1;
-    const f16x8 pb = __builtin_bit_cast(f16x8, pbits);
-    float sum_hi = 0.f, sum_lo = 0.f, zsum = 0.f;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const float pv = (float)(rr < 2 ? (rr == 0 ? as_f16x2(o0).x : as_f16x2(o0).y) : (rr == 2 ? as_f16x2(o1).x : as_f16x2(o1).y));
-        if (BITS == 8 || rr < 2) sum_hi = __builtin_fmaf(pv, 1.0f, sum_hi);
-        else sum_lo = __builtin_fmaf(pv, 1.0f, sum_lo);
-        zsum = __builtin_fmaf((float)as_f16x2(vw[rr]).y, pv, zsum);
-    }
-    const float csum = __builtin_fmaf(1024.0f, sum_hi, __builtin_fmaf(64.0f, sum_lo, zsum));
-    st.l_run = st.l_run * alpha + psum;
-    st.corr = st.corr * alpha + csum;
-    if (__any(alpha != 1.0f)) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] *= alpha;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        f16x8 a;
-        if constexpr (BITS == 8) {
-            const u32x4 w = r.v[i >> 1];
-            a = (i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y);
-        } else {
-            a = biased8(r.v[2 * sb + (i >> 2)][i & 3], mg);
-        }
-        acc[i] = mfma16x16x32(a, pb, acc[i]);
-    }
+    for (int i = 0; i < 8; ++i) acc[i] *= alpha;
 }
 
-// len: tokens the lane's query column attends over (the same in every lane at a decoding step; at prefill every column
-// has its own causal limit); len_all: the largest of them, wave-uniform.
+// Runs N0 .. N0 + NH - 1 of thirty-two tokens of a block (8-bit codes: one run, 4-bit codes: two).  qsum =
+// sum of the query's 128 values; neg_qbias = minus the sum of the conversion bias of each code position times the query
+// value it meets.  len: tokens the lane's query column attends over (the same in every lane at a decoding step; at prefill
+// every column has its own causal limit).
+//
+// PACK: at most eight query heads share the KV head.  The query operand then carries every head twice
+// (column c and c + 8 both hold head c % 8), so both score tiles of a run come out with all 16 columns live, and a lane keeps
+// tile c / 8 only - four scores instead of eight, half the softmax arithmetic.  The probabilities of the other tile's
+// tokens reach the lane through one exchange with lane c ^ 8 before the second product; running sums are per lane over
+// its own tokens and meet at the end (xor 8, 16, 32).
+template <int BITS, bool PACK, int N0, int NH>
+__device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t* sz_slot, const f16x8 (&qf)[4],
+                                              float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len,
+                                              int lane, SoftmaxState& st, f32x4 (&acc)[8])
+{
+    constexpr int NS = PACK ? 1 : 2;                         // score tiles a lane keeps of a run
+    const int h = lane >> 4, jl = PACK ? (lane >> 3) & 1 : 0;      // jl: the 16-token tile this lane keeps
+    const int rem = len - blk * (256 / BITS) - 32 * N0 - 4 * h - 16 * jl;      // slot (n, j, rr) is a live token iff 32*n + 16*j + rr < rem
+    float t[NH][NS][4];                                      // scores before the key's scale
+    f16x2 kp[NH][NS][4];                                     // (scale, zero-point) of the slot's key
+    uint32_t vw[NH][NS][4];                                  // and of its value; 0 for a dead token
+#pragma unroll
+    for (int n = 0; n < NH; ++n) {
+        // S^T for the two 16-token tiles: rows = tokens, columns = query heads.  The accumulator starts at minus the bias
+        // term: sum_d (bias_d + q_d) Q_d - sum_d bias_d Q_d = sum_d q_d Q_d
+        f32x4 d[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if constexpr (BITS == 8) {
+                d[j] = mfma16x16x32(biased8_w8(r.k[j][0].x, r.k[j][0].y), qf[0], neg_qbias);
+                d[j] = mfma16x16x32(biased8_w8(r.k[j][0].z, r.k[j][0].w), qf[1], d[j]);
+                d[j] = mfma16x16x32(biased8_w8(r.k[j][1].x, r.k[j][1].y), qf[2], d[j]);
+                d[j] = mfma16x16x32(biased8_w8(r.k[j][1].z, r.k[j][1].w), qf[3], d[j]);
+            } else {
+                const u32x4 w = r.k[N0 + n][j];
+                d[j] = mfma16x16x32(biased8(w.x, mg), qf[0], neg_qbias);
+                d[j] = mfma16x16x32(biased8(w.y, mg), qf[1], d[j]);
+                d[j] = mfma16x16x32(biased8(w.z, mg), qf[2], d[j]);
+                d[j] = mfma16x16x32(biased8(w.w, mg), qf[3], d[j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            // (K pair, V pair) of the lane's four tokens 16*(j or jl) + 4h .. +3: eight consecutive words of the slot
+            const uint32_t* const z = sz_slot + 64 * (N0 + n) + 32 * (PACK ? jl : j) + 8 * h;
+            const u32x4 p0 = *(const u32x4*)z, p1 = *(const u32x4*)(z + 4);
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                // a dead token contributes nothing, whatever its pair holds: scale 0 and zero-point 0 for its values
+                const bool live = 32 * n + 16 * j + rr < rem;
+                kp[n][j][rr] = as_f16x2(rr < 2 ? p0[2 * rr] : p1[2 * (rr - 2)]);
+                vw[n][j][rr] = live ? (rr < 2 ? p0[2 * rr + 1] : p1[2 * (rr - 2) + 1]) : 0u;
+                // sum_d q_d Q_d  -  z sum_d Q_d  =  sum_d (q_d - z) Q_d.  (Multiply-adds throughout, so that the fp16 pair
+                // enters the instruction directly; an addend of +0 keeps one from being folded into a plain multiply.)
+                const float dm = PACK ? (jl ? d[1][rr] : d[0][rr]) : d[j][rr];
+                t[n][j][rr] = __builtin_fmaf(-(float)kp[n][j][rr].y, qsum, dm);
+            }
+        }
+    }
+    // scores in base 2 (the query carries scale * log2(e)) less the reference
+    float x[NH][NS][4], mx = kNegBig;
+    auto scores = [&](float ref) {
+        mx = kNegBig;
+#pragma unroll
+        for (int n = 0; n < NH; ++n)
+#pragma unroll
+            for (int j = 0; j < NS; ++j)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const float v = __builtin_fmaf((float)kp[n][j][rr].x, t[n][j][rr], -ref);
+                    x[n][j][rr] = 32 * n + 16 * j + rr < rem ? v : kNegBig;
+                    mx = fmaxf(mx, x[n][j][rr]);
+                }
+    };
+    scores(st.m_run);
+    if (__any(mx > kSlack<BITS>)) {
+        scores(0.0f);
+        move_reference<PACK>(mx, st, acc);
+        scores(st.m_run);
+    }
+    // probability times the value scale of that token, rounded to fp16: the operand of the second product.  The correction
+    // term must be built from the very fp16 values the matrix core multiplies: the bias is about a
+    // thousand times the payload, so one fp16 ulp of disagreement on a single probability shifts a whole output row by
+    // several per cent.  Left to itself the compiler rounds p * vs once for the operand (fused multiply-and-convert)
+    // and once more, through fp32, for the sum below; the two differ when the fp32 product lands on an fp16 tie.
+    // Pinning the packed operand makes it the only copy.
+    float psum = 0.f, bsum = 0.f, zsum = 0.f;
+    f16x8 pb[NH];
+#pragma unroll
+    for (int n = 0; n < NH; ++n) {
+        uint32_t own[NS][2];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            _Float16 q[4];
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const float p = fast_exp2(x[n][j][rr]);      // 0 for masked tokens
+                psum += p;
+                q[rr] = (_Float16)__builtin_fmaf((float)as_f16x2(vw[n][j][rr]).x, p, 0.0f);
+            }
+            own[j][0] = (uint32_t)__builtin_bit_cast(uint16_t, q[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[1]) << 16);
+            own[j][1] = (uint32_t)__builtin_bit_cast(uint16_t, q[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[3]) << 16);
+            asm volatile("" : "+v"(own[j][0]), "+v"(own[j][1]));
+            // sum over the lane's tokens of (bias + z) * p' - for 4-bit codes of z * p' only, see below
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const f16x2 two = as_f16x2(own[j][rr >> 1]);
+                const float pv = (float)(rr & 1 ? two.y : two.x);
+                if (BITS == 8) bsum = __builtin_fmaf(pv, 1.0f, bsum);
+                zsum = __builtin_fmaf((float)as_f16x2(vw[n][j][rr]).y, pv, zsum);
+            }
+        }
+        u32x4 bits;                                          // k-values 0..3: tile 0, 4..7: tile 1
+        if constexpr (PACK) {
+            const uint32_t x0 = swap_half_rows(own[0][0]), x1 = swap_half_rows(own[0][1]);
+            bits.x = jl ? x0 : own[0][0];
+            bits.y = jl ? x1 : own[0][1];
+            bits.z = jl ? own[0][0] : x0;
+            bits.w = jl ? own[0][1] : x1;
+        } else {
+            bits = u32x4{own[0][0], own[0][1], own[NS - 1][0], own[NS - 1][1]};
+        }
+        pb[n] = __builtin_bit_cast(f16x8, bits);
+    }
+    st.l_run += psum;
+    st.corr += __builtin_fmaf(1024.0f, bsum, zsum);
+    if constexpr (BITS == 4) {
+        // The bias of a 4-bit value code is up to a hundred times the payload: carried along to the end of a long context it
+        // would cost the sums their low bits.  One product with the constant operand -bias (1024, or 64 at the k-values 2, 3, 6
+        // and 7 of a word) takes it out run by run, before the codes that carry it go in.
+        const _Float16 a = (_Float16)-1024.0f, b = (_Float16)-64.0f;
+        const f16x8 minus_bias = {a, a, b, b, a, a, b, b};
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int n = 0; n < NH; ++n) bias = mfma16x16x32(minus_bias, pb[n], bias);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += bias;
+    }
+    // O^T += V^T P'^T : rows = dimensions (eight 16-row tiles), k = the 32 tokens of a run
+#pragma unroll
+    for (int n = 0; n < NH; ++n)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            f16x8 a;
+            if constexpr (BITS == 8) {
+                const u32x4 w = r.v[i >> 1];
+                a = (i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y);
+            } else {
+                a = biased8(r.v[2 * (N0 + n) + (i >> 2)][i & 3], mg);
+            }
+            acc[i] = mfma16x16x32(a, pb[n], acc[i]);
+        }
+}
+
+// A whole block.  The two runs of a 4-bit block go through together, which gives each wave two independent chains of
+// instructions; with two score tiles a lane that takes more registers than there are, so there they go one after the other.
 template <int BITS, bool PACK>
 __device__ __forceinline__ void process_block(const BlockRegs& r, const uint32_t* sz_slot, const f16x8 (&qf)[4],
                                               float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len, int len_all,
                                               int lane, SoftmaxState& st, f32x4 (&acc)[8])
 {
-    constexpr int TOK = 256 / BITS;
-    const int t0 = blk * TOK;
-    // the first 32 tokens always hold a live one; the second half of a 4-bit block may lie wholly behind the context
-    // (wave-uniform).  (A second, unmasked copy of the code for blocks inside the context costs more registers than the
-    // kernel has: it spills.)
-    if constexpr (PACK) {
-        process_tokens_packed<BITS, true>(r, 0, sz_slot, qf, qsum, neg_qbias, mg, t0, len, lane, st, acc);
-        if constexpr (BITS == 4) {
-            if (t0 + 32 < len_all)
-                process_tokens_packed<4, true>(r, 1, sz_slot + 64, qf, qsum, neg_qbias, mg, t0 + 32, len, lane, st, acc);
-        }
+    if constexpr (BITS == 8 || PACK) {
+        process_runs<BITS, PACK, 0, BITS == 8 ? 1 : 2>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
     } else {
-        process_tokens<BITS, true>(r, 0, sz_slot, qf, qsum, neg_qbias, mg, t0, len, lane, st, acc);
-        if constexpr (BITS == 4) {
-            if (t0 + 32 < len_all) process_tokens<4, true>(r, 1, sz_slot + 64, qf, qsum, neg_qbias, mg, t0 + 32, len, lane, st, acc);
-        }
+        process_runs<BITS, PACK, 0, 1>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
+        if (blk * 64 + 32 < len_all)                         // (wave-uniform) the second run may lie wholly behind the context
+            process_runs<BITS, PACK, 1, 1>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
     }
 }
 
@@ -712,7 +672,7 @@ __device__ __forceinline__ void store_out4(uint16_t* O, int b, int q_heads, int 
 
 // grid (kv heads, batch, splits); 256 threads.  Partial layout per (b, h, split): m[16], l[16], out[128][16] floats.
 constexpr int kPartialFloats = 32 + kHeadDim * 16;
-constexpr int kMergeHere = 8;            // splits the last-arriving CTA merges itself (all their loads in flight at once)
+constexpr int kMergeBatch = 8;           // splits the last-arriving CTA loads at a time (all in flight at once)
 
 // PREFILL: the same kernel over a short chunk of prompt tokens, or one of few heads (paper Sec. 3.3: one attention pipeline for
 // both phases; chunks that fill the chip with 128- or 256-row CTAs run on tm_attn_prefill.hip).  The 16
@@ -746,7 +706,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int G = gw;
     const int hq = hk * (q_heads / kv.heads) + head0;
     const size_t bh = (size_t)b * kv.heads + hk;
-    int len, len_all;                                        // this lane's column; the CTA's longest column
+    int len = 0, len_all = 0;                                // this lane's column; the CTA's longest column
     int tok = 0, head = c;                                   // query token (within the chunk) and head (within G) of column c
     bool real;
     if constexpr (PREFILL) {
@@ -755,7 +715,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         head = c - tq * G;
         tok = split * tpg + tq;
         const int cnt = counts ? min(max(counts[b], 0), count) : count;
-        const int first = split * tpg;                       // first token of this group
+        const int first = split * tpg;                    // first token of this group
         if (first >= cnt) return;                            // (uniform) nothing to do for this sequence
         const int pos0 = lens[b];
         const int pos = pos0 + tok;
@@ -764,14 +724,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         len_all = min(max(pos0 + min(cnt, first + tpg), 0), kv.cap);
         if (!real) tok = first;                              // an address that exists
     } else {
-        // the splits cover blocks_per_split * splits blocks (the host's max_len): a longer sequence is cut there
-        len = min(min(max(lens[b], 0), kv.cap), blocks_per_split * splits * TOK);
-        len_all = len;
         real = (PACK ? (c & 7) : c) < G;
     }
-    const int nblk = (len_all + TOK - 1) / TOK;
+    // Blocks the loads may touch.  At a decoding step that is the whole cache of the (sequence, head): the first blocks are
+    // requested before the sequence's length is known (what lies behind it is masked), which takes one memory round trip
+    // out of a launch that is a chain of them.
+    const int nblk = PREFILL ? (len_all + TOK - 1) / TOK : kv.cap / TOK;
     const int blk0 = PREFILL ? 0 : split * blocks_per_split;
-    const int blk1 = PREFILL ? nblk : min(nblk, blk0 + blocks_per_split);
+    int blk1 = PREFILL ? nblk : min(blk0 + blocks_per_split, nblk);
 
     // Order of the prologue: the query's raw loads, then at once the first two blocks of the KV memory loading pipeline,
     // and only then the arithmetic on the query, which so runs under the blocks' latency (loads return in order, so the
@@ -801,6 +761,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int blk = blk0 + wave;
     load_block<BITS>(r0, z0, rs, blk < blk1 ? blk : nblk, lane);
     load_block<BITS>(r1, z1, rs, blk + 4 < blk1 ? blk + 4 : nblk, lane);
+    if constexpr (!PREFILL) {
+        // the splits cover blocks_per_split * splits blocks (the host's max_len): a longer sequence is cut there
+        len = len_all = min(min(max(lens[b], 0), kv.cap), blocks_per_split * splits * TOK);
+        blk1 = min(blk1, (len_all + TOK - 1) / TOK);
+    }
 
     // Query operand (adaptive head alignment): column m = c, k-values of step tt = dimensions 32h + 8tt .. +7, the
     // order in which the lane's key bytes arrive; scaled once by scale * log2(e).
@@ -923,7 +888,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     if (!merge_here) return;                                  // many splits: the merge kernel follows
 
-    // Few splits: the CTA that arrives last at this (sequence, head)'s counter merges them, in split order.
+    // The CTA that arrives last at this (sequence, head)'s counter merges the splits, in their order.
     __shared__ uint32_t s_last;
     wait_stores_done();
     __syncthreads();
@@ -933,33 +898,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     __syncthreads();
     if (!s_last) return;
-    // at most kMergeHere splits come here: all their loads are issued before the first use (the loop is unrolled and a
-    // missing split reads split 0 again with a factor of zero)
+    // kMergeBatch splits at a time: all their loads are issued before the first use (the loop is unrolled and a missing
+    // split reads split 0 again with a factor of zero)
     const float* base = kv.partial + (size_t)bh * splits * kPartialFloats;
-    float ms[kMergeHere], ls[kMergeHere], vals[kMergeHere][2][4];
-#pragma unroll
-    for (int sp = 0; sp < kMergeHere; ++sp) {
-        const float* ps = base + (size_t)(sp < splits ? sp : 0) * kPartialFloats;
-        ms[sp] = ld_partial(ps + c);
-        ls[sp] = ld_partial(ps + 16 + c);
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) vals[sp][ii][rr] = ld_partial(ps + 32 + (4 * (2 * wave + ii) + rr) * 64 + lane);
-    }
-    float Mg = kNegBig;
-#pragma unroll
-    for (int sp = 0; sp < kMergeHere; ++sp) Mg = fmaxf(Mg, sp < splits ? ms[sp] : kNegBig);
-    float Lg = 0.f;
+    float Mg = kNegBig, Lg = 0.f;
     float o[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int s0 = 0; s0 < splits; s0 += kMergeBatch) {
+        float ms[kMergeBatch], ls[kMergeBatch], vals[kMergeBatch][2][4];
 #pragma unroll
-    for (int sp = 0; sp < kMergeHere; ++sp) {
-        const float fs = sp < splits ? exp2f(ms[sp] - Mg) : 0.f;
-        Lg += ls[sp] * fs;
+        for (int sp = 0; sp < kMergeBatch; ++sp) {
+            const float* ps = base + (size_t)(s0 + sp < splits ? s0 + sp : 0) * kPartialFloats;
+            ms[sp] = ld_partial(ps + c);
+            ls[sp] = ld_partial(ps + 16 + c);
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) vals[sp][ii][rr] = ld_partial(ps + 32 + (4 * (2 * wave + ii) + rr) * 64 + lane);
+        }
+        float Mn = Mg;
+#pragma unroll
+        for (int sp = 0; sp < kMergeBatch; ++sp) Mn = fmaxf(Mn, s0 + sp < splits ? ms[sp] : kNegBig);
+        const float fg = exp2f(Mg - Mn);
+        Mg = Mn;
+        Lg *= fg;
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) o[ii][rr] += vals[sp][ii][rr] * fs;
+            for (int rr = 0; rr < 4; ++rr) o[ii][rr] *= fg;
+#pragma unroll
+        for (int sp = 0; sp < kMergeBatch; ++sp) {
+            const float fs = s0 + sp < splits ? exp2f(ms[sp] - Mg) : 0.f;
+            Lg += ls[sp] * fs;
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) o[ii][rr] += vals[sp][ii][rr] * fs;
+        }
     }
     const float invg = Lg > 0.f ? 1.0f / Lg : 0.f;
 #pragma unroll
@@ -1058,29 +1032,31 @@ hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int3
 {
     const int tok = 256 / kv.bits;                                   // tokens per 4 KiB block
     const int nblk = (max_len + tok - 1) / tok;
-    // enough CTAs for two per CU - what is resident at once with two waves per SIMD; a third would run in a second,
-    // half-empty round (measured: 28.5 instead of 31.8 us at batch 8 x 8192) - at least four blocks per wave and split,
-    // and no more partial results than the cache's workspace holds
-    int splits = (2 * num_cu + kv.batch * kv.heads - 1) / (kv.batch * kv.heads);
-    // (short contexts: up to eight splits of at least two blocks per wave - a 2048-token context is cut in four or
-    // eight instead of two or four pieces, which shortens each CTA's serial chain more than the merge costs)
-    const int few = nblk / 8 < 8 ? nblk / 8 : 8;
-    const int by_work = nblk / 16 > few ? nblk / 16 : (few > 0 ? few : 1);
+    // One CTA per CU.  A CU streams its share as fast with one CTA as with two, and what a launch waits for is the CU with
+    // the most: a second, partial round of CTAs (or lengths that leave two long ones on one CU) costs more than idle CUs do.  4-bit cache, 32
+    // sequences of 4096-8192 tokens, 8 heads: 44.7 us in two splits, 39.5 unsplit; 8-bit, 27 x 4 heads, 10-20 thousand tokens:
+    // 85 us in five, 72 in two; 109 x 4 heads, 500-1000 tokens: 21.8 in two, 14.3 unsplit.  Only where that would leave almost half the CUs
+    // idle over a long context (129 ... 140 (sequence, head) pairs) the launch has two CTAs per CU instead.
+    const int segs = kv.batch * kv.heads;
+    int splits = segs >= num_cu ? 1 : num_cu / segs;
+    if (segs > num_cu / 2 && segs * 20 <= num_cu * 11 && nblk >= 128) splits = (2 * num_cu + segs - 1) / segs;
+    // at least four blocks per wave and split (short contexts: up to eight splits of at least two - a 2048-token context
+    // is cut in four or eight instead of two or four pieces, which shortens each CTA's serial chain more than the merge
+    // costs; none below 24 blocks, where it costs more: 17 blocks 6.0 us unsplit, 7.1 in two), and no more partial results
+    // than the cache's workspace holds
+    const int few = nblk < 24 ? 1 : nblk / 8 < 8 ? nblk / 8 : 8;
+    const int by_work = nblk / 16 > few ? nblk / 16 : few;
     if (splits > by_work) splits = by_work;
     if (splits > kv.max_splits) splits = kv.max_splits;
-    // four splits merge without a second launch: worth more than a fuller second half-round as soon as four splits
-    // give every CU a CTA (batch 8 x 8192: 26.4 instead of 29.3 us; at batch 1 the GPU would be left mostly empty)
-    if (splits > 4 && kv.batch * kv.heads * 4 >= num_cu) splits = 4;
-    if (splits < 1) splits = 1;
     const int bps = (nblk + splits - 1) / splits;
     splits = (nblk + bps - 1) / bps > 0 ? (nblk + bps - 1) / bps : 1;
     if (kv.heads > 65535 || kv.batch > 65535) return hipErrorInvalidValue;
     const float scale_log2e = scale * 1.4426950408889634f;
-    // up to eight splits are merged by the CTA that finishes last, with all its loads in flight at once (two splits:
+    // up to sixteen splits are merged by the CTA that finishes last, eight loads in flight at once (two splits:
     // 27.6 instead of 29.7 us at batch 32 x 2048; a loop over the splits, one load chain after the other, cost 11.5
     // instead of 8.5 us at batch 1 x 2048); more splits go to the merge kernel, which spreads a (sequence, head) over
     // eight CTAs
-    const int merge_here = splits > 1 && splits <= kMergeHere;
+    const int merge_here = splits > 1 && splits <= 2 * kMergeBatch;
     const dim3 grid(kv.heads, kv.batch, splits);
     // one pass per sixteen query heads of a KV head's group (the sixteen columns of an MFMA tile); the passes follow
     // each other on the stream and share the cache's split workspace

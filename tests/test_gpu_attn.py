@@ -238,6 +238,49 @@ def test_attn_decode_full_size_sampled(tm, bits):
     cache.close()
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,Hkv,G,T,bound", [
+    (2, 14, 4, 4800, 0),       # 28 (sequence, head) pairs: nine splits, merged by the last CTA in two batches (4-bit: eight or fewer)
+    (1, 16, 2, 16384, 0),      # sixteen splits (4-bit: the same)
+    (1, 3, 2, 16384, 0),       # more than sixteen: the merge kernel
+    (2, 66, 1, 8192, 0),       # 132 pairs over a long context: two CTAs per CU
+    (5, 60, 9, 700, 300),      # more pairs than CUs: no split; a bound below the lengths
+])
+def test_attn_decode_splits(tm, B, Hkv, G, T, bound, bits):
+    """Every way a context is split and merged, with scores that grow along the context (the running reference has to move
+    again and again, the merge has to weigh splits far apart), a sequence of one token and one without any."""
+    import torch
+    _say(f"attn decode splits B={B} Hkv={Hkv} G={G} T={T} bits={bits}")
+    rng = np.random.default_rng(T + Hkv + bits)
+    g = torch.Generator(device="cuda").manual_seed(T + bits)
+    K, V = (torch.randn((B, T, Hkv, 128), generator=g, device="cuda").to(torch.float16) for _ in range(2))
+    Q = torch.randn((B, Hkv * G, 128), generator=g, device="cuda").to(torch.float16)
+    direction = Q.view(B, 1, Hkv, G, 128)[:, :, :, 0].float()
+    K = (K.float() + torch.linspace(-1.0, 1.0, T, device="cuda").view(1, T, 1, 1) * direction).to(torch.float16)
+    lens = np.array([T] + [0, 1, T // 2, T - 1][:B - 1], np.int32)
+    cache = tm.tm_kv_create(B, Hkv, T, bits)
+    for t in range(0, T, 2048):
+        tm.tm_kv_append(cache, K[:, t:t + 2048].contiguous(), V[:, t:t + 2048].contiguous(), torch.full((B,), t, dtype=torch.int32, device="cuda"))
+    outs = []
+    for _ in range(3):
+        O = torch.full((B, Hkv * G, 128), float("nan"), dtype=torch.float16, device="cuda")
+        tm.tm_attn_decode(Q, cache, _dev(lens), O, 128 ** -0.5, max_len=bound)
+        torch.cuda.synchronize()
+        outs.append(O.cpu().numpy())
+    assert all(np.array_equal(outs[0].view(np.uint16), o.view(np.uint16)) for o in outs[1:])
+    seen = lens if not bound else np.minimum(lens, -(-bound // (256 // bits)) * (256 // bits))
+    for b in range(B):
+        if seen[b] == 0:
+            assert not outs[0][b].any()
+            continue
+        hk = int(rng.integers(Hkv))
+        k, v = (x[b:b + 1, :, hk:hk + 1].permute(0, 2, 1, 3).contiguous().cpu().numpy() for x in (K, V))
+        ref = oa.attn_decode(Q[b:b + 1, hk * G:(hk + 1) * G].cpu().numpy(), *oa.kv_quantise(k, bits), *oa.kv_quantise(v, bits), seen[b:b + 1], 128 ** -0.5)
+        ok, worst, fro = _close(outs[0][b:b + 1, hk * G:(hk + 1) * G], ref)
+        assert ok, (b, worst, fro)
+    cache.close()
+
+
 def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
