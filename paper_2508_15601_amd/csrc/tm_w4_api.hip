@@ -1151,13 +1151,24 @@ void tm_free_expert_group(tm_expert_group* group)
     delete group;
 }
 
-// Decode batches of 4-bit experts (at most about sixteen rows per expert): the one-shot kernels, launched as the
+// Decode batches of 4-bit experts (at most about sixteen rows per expert): the one-shot kernels.  Few rows per expert: their
+// small CTAs (stream_grouped_form).  Otherwise launched as the
 // single-GEMM plan of one expert at sixteen rows would launch them, once per expert that has rows (8 experts of
 // 4096 x 28672, 2 rows: 27 us against 32 us on the ring-buffered grouped kernel).  False: no such plan.
-static bool grouped_one_shot(const tm_expert_group* group, int variant, int strips, int num_cu, Plan* one)
+static bool grouped_one_shot(const tm_expert_group* group, int total_rows, int variant, int strips, int num_cu, Plan* one, int* pass_log,
+                             int* lds)
 {
     if (group->bits != 4 || !is_skinny(variant) || skinny_rows(variant) != 16 || g_force_variant >= 0 || g_force_stage == 1) return false;
     const int KU = group->K / kUnitK, NT = group->N / kUnitN;
+    const double mean = (double)total_rows / group->experts;
+    const int active = total_rows < group->experts ? total_rows : group->experts;
+    // (mean + two standard deviations of a balanced routing: one expert in thirty or so takes a second pass)
+    if (g_force_waves == 0 && stream_grouped_form(NT, KU, group->group, active, mean + 2.0 * sqrt(mean), num_cu, one, pass_log, lds)) {
+        one->variant = variant;
+        return true;
+    }
+    *pass_log = 4;
+    int red_off;
     // large experts: the strips the single-GEMM plan of one expert takes at sixteen rows, as long as a CTA still streams
     // 128 KiB of weights or more (8 experts of 4096 x 28672, 8 rows: 63.9 us on 256 strips per expert against 70.5 us
     // on the 224 strips of the grouped plan); small experts keep the grouped plan's wider strips (128 experts of
@@ -1172,6 +1183,7 @@ static bool grouped_one_shot(const tm_expert_group* group, int variant, int stri
         if (single.stream_ni > 0 && single.split == 1 && is_skinny(single.variant) && skinny_rows(single.variant) == 16 &&
             (size_t)group->K * group->N / 2 / single.strips >= 128 * 1024) {
             *one = single;
+            *lds = (int)stream_lds(one->stream_ni, 4, ceil_div(NT, one->strips), (int)one->block / 64, &red_off);
             return true;
         }
     }
@@ -1180,7 +1192,6 @@ static bool grouped_one_shot(const tm_expert_group* group, int variant, int stri
     for (int w : {16, 8}) {
         if (g_force_waves >= 8 && w != g_force_waves) continue;
         const int ni = stream_units_per_wave(widest, group->group, KU, w);
-        int red_off;
         if (ni > 0 && stream_lds(ni, 4, widest, w, &red_off) <= kStreamLdsBudget) {
             *one = Plan{};
             one->variant = variant;
@@ -1188,6 +1199,7 @@ static bool grouped_one_shot(const tm_expert_group* group, int variant, int stri
             one->split = 1;
             one->stream_ni = ni;
             one->block = (unsigned)w * 64;
+            *lds = (int)stream_lds(ni, 4, widest, w, &red_off);
             return true;
         }
     }
@@ -1232,12 +1244,12 @@ static int run_grouped(const uint16_t* X, const tm_expert_group* group, const in
         return fail(TM_EINVAL, "total_rows*K must be below 2^31 for prefill-sized expert loads");
     hipError_t e;
     Plan one;
-    if (grouped_one_shot(group, variant, strips, g_dev[dev].num_cu, &one)) {
-        int red_off;
+    int pass_log;
+    if (grouped_one_shot(group, total_rows, variant, strips, g_dev[dev].num_cu, &one, &pass_log, &gp.lds_bytes)) {
         gp.strips = one.strips;
         gp.strip_base = gp.NT / one.strips;
         gp.strip_rem = gp.NT % one.strips;
-        gp.lds_bytes = (int)stream_lds(one.stream_ni, 4, ceil_div(gp.NT, one.strips), (int)one.block / 64, &red_off);
+        gp.pass_rows = 1 << pass_log;
         e = launch_stream_grouped(gp, group->experts, group->group, one.stream_ni, (int)one.block, (hipStream_t)stream);
         if (e != hipSuccess) return fail_hip(e, "grouped kernel launch");
         return TM_OK;

@@ -112,6 +112,7 @@ hipError_t stream_grouped_setup();                                     // the sa
 hipError_t launch_stream_grouped(const GroupedParams& gp, int experts, int group, int ni, int block, hipStream_t stream);
 int stream_units_per_wave(int ntw, int group, int kus, int waves);     // 0: no one-shot kernel is built for this shape
 constexpr size_t kStreamLdsBudget = 156 * 1024;                       // of the 160 KiB of a CU
+bool stream_grouped_form(int NT, int KU, int group, int active, double rows, int num_cu, Plan* one, int* pass_log, int* lds);
 size_t stream_lds(int ni, int mp_log, int ntw, int waves, int* red_off);
 hipError_t launch_rows(const GemmParams& p, const Plan& plan, int group, hipStream_t stream);      // 16 < M <= 64
 hipError_t launch_rows32(const GemmParams& p, const Plan& plan, int group, hipStream_t stream);

@@ -282,11 +282,18 @@ __global__ __launch_bounds__(MAXW * 64) void stream_kernel(GemmParams p)
 }
 
 // Grouped (mixture-of-experts) form of the one-shot kernels: blockIdx.y selects among the experts that have rows, as in
-// skinny_grouped_kernel; an expert's rows are taken sixteen at a time, each pass a one-shot GEMM of its own (so the form
-// is meant for decode batches, where an expert seldom has more than sixteen rows).  The LDS of the launch is sized for
-// sixteen rows; the reduction tiles lie behind the X regions of the pass where both fit.
+// skinny_grouped_kernel; an expert's rows are taken pass_rows at a time, each pass a one-shot GEMM of its own (so the form
+// is meant for decode batches, where an expert seldom has more).  The LDS of the launch is sized for that many rows; the
+// reduction tiles lie behind the X regions of the pass where both fit.
+//
+// Many CTAs run one after the other on a CU here, each with a beginning (requests, first bytes) and an end (the sum over the
+// waves) that stream nothing.  So the CTAs are kept small enough for several to be resident - while one begins or ends, the
+// others stream: up to 64 registers of weights in flight per lane and 160 KiB of LDS for sixteen waves (two CTAs of eight or
+// four of four).  128 experts of 4096 x 3072 and 1536 x 4096 of which 82 have one or two rows: 117 -> 94-100 us on CTAs of eight
+// waves and three column tiles instead of eight, 72 -> 51 us (5.4 TB/s) on four waves and three tiles instead of sixteen and eight.
 template <int NTW, int GPU, int NI, int MAXW>
-__global__ __launch_bounds__(MAXW * 64) void stream_grouped_kernel(GroupedParams gp)
+__global__ __launch_bounds__(MAXW * 64) __attribute__((amdgpu_waves_per_eu(NTW * NI * (4 + GPU) <= 64 ? 4 : 2))) void stream_grouped_kernel(
+    GroupedParams gp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
     __shared__ uint32_t s_last;
@@ -296,11 +303,11 @@ __global__ __launch_bounds__(MAXW * 64) void stream_grouped_kernel(GroupedParams
     const int strip = blockIdx.x;
     const int nt0 = strip * gp.strip_base + min(strip, gp.strip_rem);
     const bool narrow = NTW > 1 && strip >= gp.strip_rem && gp.strip_base < NTW;      // CTA-uniform
-    for (int m0 = er.r0; m0 < er.r1; m0 += 16) {
+    for (int m0 = er.r0; m0 < er.r1; m0 += gp.pass_rows) {
         if (m0 != er.r0) __syncthreads();           // the previous pass is done with LDS
         p.X = gp.X + (size_t)m0 * gp.K;
         p.Y = gp.Y + (size_t)m0 * p.ldy;
-        p.M = min(16, er.r1 - m0);
+        p.M = min(gp.pass_rows, er.r1 - m0);
         p.mp_log = p.M > 8 ? 4 : p.M > 4 ? 3 : p.M > 2 ? 2 : p.M > 1 ? 1 : 0;
         const int x_bytes = ((((NI << p.mp_log) + 3) >> 2) << 10) * MAXW;
         const int red_bytes = MAXW * NTW * 4 * 64 * (int)sizeof(float);
@@ -365,10 +372,18 @@ hipError_t stream_raise_one()
     }
 }
 
+// The grouped form is built for CTAs of four waves too, and for CTAs of eight with few weights in flight: narrow strips only.
+constexpr bool grouped_built(int ntw, int gpu, int ni, int maxw)
+{
+    const int inflight = ni * ntw * (4 + gpu);
+    if (maxw == 4) return ntw <= 3 && ni <= 4 && inflight <= 48;
+    return stream_built(ntw, gpu, ni, maxw) || (maxw == 8 && ntw <= 4 && inflight <= 64);
+}
+
 template <int NTW, int GPU, int NI, int MAXW>
 hipError_t launch_stream_grouped_one(const GroupedParams& gp, int experts, int block, hipStream_t stream)
 {
-    if constexpr (stream_built(NTW, GPU, NI, MAXW)) {
+    if constexpr (grouped_built(NTW, GPU, NI, MAXW)) {
         dim3 grid(gp.strips, gp.total_rows < experts ? gp.total_rows : experts);
         if (block != MAXW * 64) return hipErrorInvalidValue;
         hipLaunchKernelGGL((stream_grouped_kernel<NTW, GPU, NI, MAXW>), grid, dim3(block), gp.lds_bytes, stream, gp);
@@ -381,7 +396,7 @@ hipError_t launch_stream_grouped_one(const GroupedParams& gp, int experts, int b
 template <int NTW, int GPU, int NI, int MAXW>
 hipError_t stream_grouped_raise_one()
 {
-    if constexpr (stream_built(NTW, GPU, NI, MAXW)) {
+    if constexpr (grouped_built(NTW, GPU, NI, MAXW)) {
         return hipFuncSetAttribute((const void*)stream_grouped_kernel<NTW, GPU, NI, MAXW>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStreamLdsBudget);
     } else {

@@ -842,6 +842,26 @@ def test_grouped_gemm_against_oracle(tm, oracle, E, K, N, g, counts, lead, trail
         p.close()
 
 
+# decode-sized loads on the small CTAs of the one-shot form: four waves (K up to 2048) and eight (up to 4096), one to four units
+# per wave with a ragged last one, every strip width, and experts with more rows than a pass takes (eight or sixteen)
+GROUPED_SMALL_CASES = [
+    # E, K, N, g, rows per expert
+    (12, 128, 1040, 128, [0, 1, 17, 0, 2, 0, 0, 1, 0, 0, 0, 3]),
+    (12, 640, 4112, 64, [2, 0, 0, 1, 33, 0, 1, 0, 0, 0, 1, 0]),
+    (9, 1152, 2064, 128, [0, 9, 0, 1, 8, 0, 0, 0, 1]),
+    (9, 1664, 528, 32, [1, 0, 10, 0, 0, 1, 0, 0, 4]),
+    (9, 2048, 3088, 128, [1, 0, 0, 0, 17, 1, 0, 2, 0]),
+    (6, 2176, 3600, 128, [9, 1, 0, 0, 2, 0]),
+    (6, 3072, 272, 64, [0, 8, 1, 0, 0, 1]),
+    (6, 4096, 1552, 128, [1, 0, 16, 0, 0, 2]),
+]
+
+
+@pytest.mark.parametrize("E,K,N,g,counts", GROUPED_SMALL_CASES)
+def test_grouped_gemm_small_ctas_against_oracle(tm, oracle, E, K, N, g, counts):
+    test_grouped_gemm_against_oracle(tm, oracle, E, K, N, g, counts, 1, 2, -1)
+
+
 # the same launch over 8-bit integer and FP8 experts: decode-sized loads (every strip width the dispatcher picks), loads
 # taken in passes, prefill-sized loads on both CTA tiles
 GROUPED_8BIT_CASES = [
