@@ -216,15 +216,61 @@ static bool deep_narrow_tile64(const tm_packed_w4* h, int M, int num_cu)
            g_force_variant < 0 && g_force_split == 0 && g_force_waves == 0 && g_force_stage == 0;
 }
 
+// The CTA tile of an 8-bit launch of more than 64 rows: the largest one that gives every CU a CTA, unless another is estimated
+// to be faster by 8 % or more.  What the first rule does not see is the last round: K = 4096, N = 12288, M = 700 (FP8) makes 288
+// tiles of 128 x 256, 32 of which run while the other CUs wait (97.8 us; 81.9 us on 1056 tiles of 64 x 128).  The estimate is a
+// least-squares fit to the unsplit ones of 12000 timed plans of 1968 random layers (K 1024 ... 28672, N 1024 ... 32768, M 65 ... 4096,
+// int8 and FP8, every group; rms error 5-9 %): a fixed part, the K loop (apart for launches of one round, whose CTAs have more wave sets,
+// and of several; per round, and by the load on average), more of it where groups of 32 double the scales, and the output's store.
+// On 3690 other random layers it changes every fourth choice: those run 1.20 times as fast on average, one of them 5 % slower.  Launches that the first rule leaves so small that K may be split keep that rule's tile, and no other tile is taken
+// that may split: a call needs the scratch it always did.
+static int choose_tile_8bit(int M, int K, int N, int group, int num_cu)
+{
+    struct Shape {
+        int variant;
+        double one[3];                  // us: fixed, per 1024 rows of K, per 1024 rows of K and share of the CUs in use
+        double more[3];                 // fixed, per 1024 rows and round, per 1024 rows and CTAs per CU
+        double fine, out;               // per 1024 rows and CTAs per CU in groups of 32; per million outputs
+    };
+    static const Shape shapes[4] = {
+        {kTile128x256, {7.03, 8.96, 4.33}, {7.13, 8.98, 3.50}, 2.04, 0.49},
+        {kTile128x128, {4.94, 5.40, 3.39}, {5.66, 4.70, 2.68}, 0.48, 0.51},
+        {kTile64x128, {4.35, 3.21, 1.71}, {6.48, 2.76, 1.60}, 0.45, 0.26},
+        {kTile32x128, {4.15, 2.24, 1.34}, {5.07, 1.89, 1.24}, 0.46, 0.01}};
+    auto ctas = [&](int v) { return (long)ceil_div(M, tile_bm(v)) * ceil_div(N, tile_bn(v)); };
+    const int first = ctas(kTile128x256) >= num_cu ? kTile128x256 : ctas(kTile64x128) >= num_cu ? kTile64x128 : kTile32x128;
+    if (ctas(first) * 2 <= num_cu) return first;
+    auto estimate = [&](const Shape& s) {
+        const long c = ctas(s.variant);
+        const double k = K / 1024.0, load = (double)c / num_cu;
+        const double loop = c <= num_cu ? s.one[0] + k * (s.one[1] + s.one[2] * load)
+                                        : s.more[0] + k * (s.more[1] * (double)((c + num_cu - 1) / num_cu) + s.more[2] * load);
+        return loop + (group == 32 ? s.fine * k * (load > 1.0 ? load : 1.0) : 0.0) + s.out * M * 1e-6 * N;
+    };
+    double least = 0.0;
+    for (const Shape& s : shapes)
+        if (s.variant == first) least = 0.92 * estimate(s);
+    int best = first;
+    for (const Shape& s : shapes) {
+        if (s.variant == first || ctas(s.variant) * 2 <= num_cu) continue;
+        const double e = estimate(s);
+        if (e < least) {
+            least = e;
+            best = s.variant;
+        }
+    }
+    return best;
+}
+
 static int choose_variant(const tm_packed_w4* h, int M, int num_cu, int NT)
 {
     const bool w8 = h->bits == 8;
     int variant = g_force_variant;
-    // 8-bit formats: the decode kernels up to 64 rows, three CTA-tile shapes above
+    // 8-bit formats: the decode kernels up to 64 rows, four CTA-tile shapes above
     if (w8 && variant >= 0 && !(variant == kSkinny16x16 || variant == kSkinny16x32 || variant == kSkinny16x48 ||
                                 variant == kSkinny16x64 || variant == kSkinny16x96 || variant == kSkinny16x128 ||
                                 variant == kSkinny32x64 || variant == kSkinny64x64 || variant == kTile32x128 ||
-                                variant == kTile64x128 || variant == kTile128x256))
+                                variant == kTile64x128 || variant == kTile128x128 || variant == kTile128x256))
         variant = -1;
     if (variant < 0 && w8 && M > 16) {
         auto ctas = [&](int v) { return (long)ceil_div(M, tile_bm(v)) * ceil_div(h->N, tile_bn(v)); };
@@ -233,9 +279,7 @@ static int choose_variant(const tm_packed_w4* h, int M, int num_cu, int NT)
         const bool narrow = ceil_div(NT, 4) * 2 <= num_cu;
         if (M <= 32) variant = narrow ? kSkinny32x64 : kTile32x128;
         else if (M <= 64) variant = narrow ? kSkinny64x64 : kTile64x128;
-        else if (ctas(kTile128x256) >= num_cu) variant = kTile128x256;
-        else if (ctas(kTile64x128) >= num_cu) variant = kTile64x128;
-        else variant = kTile32x128;
+        else variant = choose_tile_8bit(M, h->K, h->N, h->group, num_cu);
     } else if (variant < 0) {
         if (M <= 16) {
             // One CTA per CU: the column tiles are dealt evenly over min(NT, #CU) strips (widths differ by at most

@@ -1,5 +1,5 @@
 // CTA-tile kernels instantiated for the 8-bit weight formats (integer codes and FP8 E4M3): the same body with two packed
-// words per MFMA step and packed units of 64 rows.  Three tile shapes with one or two wave sets (four on the 32-row
+// words per MFMA step and packed units of 64 rows.  Four tile shapes with one or two wave sets (four on the 32-row
 // tile), built like the small 4-bit tiles.
 #include "tm_w4_tile_impl.h"
 
@@ -15,6 +15,7 @@ hipError_t launch_fmt(const GemmParams& p, const Plan& plan, int group, hipStrea
         switch (plan.variant) {
             case kTile32x128: return launch_shape<2, 2, 4, 4, 2, FMT>(p, plan, group, stream);
             case kTile64x128: return launch_shape<4, 2, 4, 4, 2, FMT>(p, plan, group, stream);
+            case kTile128x128: return launch_shape<8, 2, 4, 4, 2, FMT>(p, plan, group, stream);
             case kTile128x256: return launch_shape<8, 4, 4, 2, 2, FMT>(p, plan, group, stream);
             default: return hipErrorInvalidValue;
         }
@@ -28,6 +29,7 @@ hipError_t launch_fmt(const GemmParams& p, const Plan& plan, int group, hipStrea
     switch (plan.variant) {
         case kTile32x128: return launch_shape<2, 2, 4, 4, 1, FMT>(p, plan, group, stream);
         case kTile64x128: return launch_shape<4, 2, 4, 4, 1, FMT>(p, plan, group, stream);
+        case kTile128x128: return launch_shape<8, 2, 4, 4, 1, FMT>(p, plan, group, stream);
         case kTile128x256: return launch_shape<8, 4, 4, 2, 1, FMT>(p, plan, group, stream);
         default: return hipErrorInvalidValue;
     }

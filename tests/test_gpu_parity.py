@@ -1108,6 +1108,35 @@ def test_fp8_every_code_converts_exactly(tm, oracle):
     packed.close()
 
 
+@pytest.mark.parametrize("fmt", ["int8", "fp8"])
+@pytest.mark.parametrize("M,K,N,g,variant,waves", [
+    # the 128 x 128 tile, one and two wave sets: whole and ragged tiles, K that leaves two sets no whole stage, each group
+    (128, 512, 128, 128, 10, 4), (128, 512, 128, 32, 10, 8), (129, 384, 144, 64, 10, 8), (255, 128, 1040, 128, 10, 0), (65, 1152, 272, 32, 10, 4),
+    # left to the dispatcher, on layers where the largest tile that fills the chip is not the one taken
+    (700, 512, 12288, 128, -1, 0), (300, 384, 17040, 64, -1, 0)])
+def test_8bit_tiles_above_64_rows(tm, oracle, fmt, M, K, N, g, variant, waves):
+    _say(f"8-bit tiles {fmt} M={M} K={K} N={N} g={g} variant={variant} waves={waves}")
+    rng = np.random.default_rng(M + K + N + g)
+    X = (rng.standard_normal((M, K)) * (0.25 if fmt == "fp8" else 1.0)).astype(np.float16)
+    if fmt == "int8":
+        q, s, z = _w8_case(rng, K, N, g)
+        packed, ref = _pack_w8(tm, q, s, z, g), oracle.gemm(X, q, s, z, g)
+    else:
+        q, s = _fp8_case(rng, K, N, g)
+        packed, ref = tm.tm_pack_w8_fp8(gu.to_dev(wl.pack_interchange8(q)), gu.to_dev(s), K, N, g), oracle.gemm_fp8(X, q, s, g)
+    tm.tm_set_variant(variant, 1 if variant == 10 else 0)
+    tm.tm_set_launch(waves, 0)
+    try:
+        plan = tm.tm_get_plan(packed, M)
+        assert plan["split_k"] == 1 and plan["variant"] in ((10,) if variant == 10 else (9, 10, 13)), plan
+        ok, worst, fro = acceptance(gu.gemm(packed, X), ref)
+    finally:
+        tm.tm_set_variant(-1, 0)
+        tm.tm_set_launch(0, 0)
+    assert ok, (worst, fro)
+    packed.close()
+
+
 @pytest.mark.parametrize("g", [32, 64, 128])
 @pytest.mark.parametrize("M,K,N,variant,split", [
     (1, 1024, 528, -1, 0), (8, 768, 4112, -1, 0), (16, 2048, 1040, -1, 0), (11, 1280, 336, 1, 2), (16, 1024, 1552, 14, 0),
