@@ -286,13 +286,19 @@ PyObject* attn_decode(PyObject*, PyObject* const* a, Py_ssize_t n)   // Q, cache
 PyObject* attn_prefill(PyObject*, PyObject* const* a, Py_ssize_t n)  // Q, cache, positions, O, scale, counts, stream
 {
     return entry(n, 7, n > 3 ? a[3] : Py_None, [&] {
-        const at::Tensor &Q = tensor(a[0], "Q"), &O = tensor(a[3], "O");
+        const at::Tensor &Q = tensor(a[0], "Q"), &O = tensor(a[3], "O"), &pos = tensor(a[2], "positions");
+        const at::Tensor* counts = a[5] == Py_None ? nullptr : &tensor(a[5], "counts");
         if (Q.dim() != 4 || Q.size(3) != 128 || O.sizes() != Q.sizes())
             raise(PyExc_ValueError, "Q and O must be [batch][count][q_heads][128]");
-        const auto* c = a[5] == Py_None ? nullptr : (const int32_t*)device_ptr(tensor(a[5], "counts"), at::kInt, "counts");
+        // The launch covers every sequence of the cache, and the C ABI cannot see how long an array is: a shorter one would be
+        // read, and O written, out of range.  (A longer one is fine: its first `batch` entries count.)
+        const int64_t batch = int_attr(a[1], s_batch);
+        if (Q.size(0) < batch || pos.numel() < batch || (counts && counts->numel() < batch))
+            raise(PyExc_ValueError, "Q / O / positions / counts have fewer sequences than the cache");
+        const auto* c = counts ? (const int32_t*)device_ptr(*counts, at::kInt, "counts") : nullptr;
         const uint16_t* q = half_ptr(Q, "Q");
         const auto* h = (const tm_kv_cache*)handle_of(a[1], kCacheFreed);
-        const auto* p = (const int32_t*)device_ptr(tensor(a[2], "positions"), at::kInt, "positions");
+        const auto* p = (const int32_t*)device_ptr(pos, at::kInt, "positions");
         uint16_t* o = half_ptr(O, "O");
         const float scale = (float)as_double(a[4]);
         const tm_stream st = stream_of(a[6]);

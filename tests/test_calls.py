@@ -42,6 +42,14 @@ def test_arguments_are_refused(call, error):
         call()
 
 
+@pytest.mark.parametrize("batch, positions, counts", [(1, 2, None), (2, 1, None), (2, 2, 1), (1, 1, 1), (0, 2, 2)])
+def test_prompt_attention_refuses_fewer_sequences_than_the_cache_has(batch, positions, counts):
+    q, at = half(batch, 3, 8, 128), torch.zeros(positions, dtype=torch.int32)
+    with pytest.raises(ValueError, match="sequences"):
+        tm.tm_attn_prefill(q, CACHE, at, half(batch, 3, 8, 128), 1.0,
+                           counts=None if counts is None else torch.zeros(counts, dtype=torch.int32))
+
+
 @pytest.mark.parametrize("empty", [lambda: tm.tm_gemm_w4a16(half(0, 256), PACKED, half(0, 32)),
                                    lambda: tm.tm_gemm_w4a16_ex(half(0, 256), PACKED, half(0, 32))])
 def test_no_rows_is_a_no_op_that_returns_the_output(empty):
