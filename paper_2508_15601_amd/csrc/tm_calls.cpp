@@ -29,17 +29,23 @@ struct Failed {};                                        // a Python exception i
     throw Failed{};
 }
 
+// int(o) and float(o): everything the two builtins take.
 long long as_int(PyObject* o)
 {
-    const long long v = PyLong_AsLongLong(o);
+    PyObject* n = PyLong_CheckExact(o) ? (Py_INCREF(o), o) : PyNumber_Long(o);
+    if (!n) throw Failed{};
+    const long long v = PyLong_AsLongLong(n);
+    Py_DECREF(n);
     if (v == -1 && PyErr_Occurred()) throw Failed{};
     return v;
 }
 
 double as_double(PyObject* o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Failed{};
+    PyObject* f = PyFloat_CheckExact(o) ? (Py_INCREF(o), o) : PyNumber_Float(o);
+    if (!f) throw Failed{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return v;
 }
 
@@ -300,7 +306,9 @@ PyObject* attn_prefill(PyObject*, PyObject* const* a, Py_ssize_t n)  // Q, cache
         const auto* h = (const tm_kv_cache*)handle_of(a[1], kCacheFreed);
         const auto* p = (const int32_t*)device_ptr(pos, at::kInt, "positions");
         uint16_t* o = half_ptr(O, "O");
-        const float scale = (float)as_double(a[4]);
+        const double scale_d = PyFloat_AsDouble(a[4]);                     // a number: no text here, unlike float()
+        if (scale_d == -1.0 && PyErr_Occurred()) throw Failed{};
+        const float scale = (float)scale_d;
         const tm_stream st = stream_of(a[6]);
         call([&] { return tm_attn_prefill(q, h, p, c, (int)Q.size(1), o, (int)Q.size(2), scale, st); });
     });

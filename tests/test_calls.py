@@ -54,3 +54,28 @@ def test_prompt_attention_refuses_fewer_sequences_than_the_cache_has(batch, posi
                                    lambda: tm.tm_gemm_w4a16_ex(half(0, 256), PACKED, half(0, 32))])
 def test_no_rows_is_a_no_op_that_returns_the_output(empty):
     assert tuple(empty().shape) == (0, 32)
+
+
+class Whole:
+    """Converts with int() and has no __index__."""
+
+    def __int__(self):
+        return 1
+
+
+@pytest.mark.parametrize("number", [1, 1.0, True, Whole(), "1", torch.tensor(1)])
+def test_numbers_are_taken_as_int_and_float_take_them(number):
+    """act, max_len and scale: the call gets past its conversions, to the freed handle."""
+    wide, narrow = half(2, 256), half(2, 16)
+    assert tm.tm_gemm_w4a16_ex(half(0, 256), PACKED, half(0, 16), act=number).shape == (0, 16)
+    assert tm.tm_gemm_w4a16_grouped_act(half(0, 256), GROUP, OFF, half(0, 16), act=number).shape == (0, 16)
+    with pytest.raises(TypeError, match="device tensor"):
+        tm.tm_gemm_w4a16_ex(wide, PACKED, narrow, act=number)
+    with pytest.raises(TypeError, match="device tensor"):
+        tm.tm_attn_decode(half(2, 8, 128), CACHE, OFF[:2], half(2, 8, 128), 1.0, max_len=number)
+
+
+@pytest.mark.parametrize("bad, error", [(None, TypeError), ("x", ValueError), ([1], TypeError)])
+def test_what_int_refuses_is_refused(bad, error):
+    with pytest.raises(error):
+        tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 16), act=bad)
