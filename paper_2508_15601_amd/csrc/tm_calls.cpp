@@ -8,6 +8,7 @@
 // Tensors are checked as the binding promises: device tensor and data type (TypeError), contiguous and of the shape the
 // handle asks for (ValueError), errors of the library as TmError.  The interpreter lock is released during the library
 // call.
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 
@@ -88,8 +89,9 @@ void* device_ptr(const at::Tensor& t, at::ScalarType type, const char* what)
         throw Failed{};
     }
     if (t.scalar_type() != type) {
-        PyErr_Format(PyExc_TypeError, "%s must have dtype torch.%s", what,
-                     type == at::kHalf ? "float16" : type == at::kInt ? "int32" : "uint8");
+        PyErr_Format(PyExc_TypeError, "%s must have dtype torch.%s, got %S", what,
+                     type == at::kHalf ? "float16" : type == at::kInt ? "int32" : "uint8",
+                     (PyObject*)torch::getTHPDtype(t.scalar_type()));
         throw Failed{};
     }
     if (!t.is_contiguous()) {

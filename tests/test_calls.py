@@ -79,3 +79,9 @@ def test_numbers_are_taken_as_int_and_float_take_them(number):
 def test_what_int_refuses_is_refused(bad, error):
     with pytest.raises(error):
         tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 16), act=bad)
+
+
+@pytest.mark.gpu
+def test_a_wrong_dtype_is_named():
+    with pytest.raises(TypeError, match="X must have dtype torch.float16, got torch.float32"):
+        tm.tm_gemm_w4a16(torch.zeros(1, 256, device="cuda"), PACKED, half(1, 32).cuda())
