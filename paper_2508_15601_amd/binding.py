@@ -11,6 +11,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libtm_w4.so")
+_CALLS_PATH = os.path.join(_HERE, "tm_calls.so")
 _lib = None
 _calls = None              # the native extension, loaded with the library
 
@@ -39,8 +40,9 @@ def load_library():
     # PyTorch-ROCm ships its own HIP runtime (same soname as the system one).  Import torch first so that the
     # library binds to the runtime torch's allocator and streams live in; two runtimes in one process see no device.
     import torch  # noqa: F401
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` first")
+    for path in (_LIB_PATH, _CALLS_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` first")
     lib = ctypes.CDLL(_LIB_PATH)
     c = ctypes
     vp, sz, i = c.c_void_p, c.c_size_t, c.c_int

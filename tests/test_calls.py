@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2508_15601_amd as tm
+from paper_2508_15601_amd import binding
 
 
 def half(*shape):
@@ -79,6 +80,15 @@ def test_numbers_are_taken_as_int_and_float_take_them(number):
 def test_what_int_refuses_is_refused(bad, error):
     with pytest.raises(error):
         tm.tm_gemm_w4a16_ex(half(2, 256), PACKED, half(2, 16), act=bad)
+
+
+@pytest.mark.parametrize("path", ["_LIB_PATH", "_CALLS_PATH"])
+def test_a_missing_build_is_named_with_the_way_to_make_it(path, tmp_path, monkeypatch):
+    tm.load_library()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, path, str(tmp_path / "not_built.so"))
+    with pytest.raises(ImportError, match="not_built.so is missing: run .*build"):
+        tm.load_library()
 
 
 @pytest.mark.gpu
