@@ -12,8 +12,8 @@
 //     leaves its registers either; the cache stores V in blocks of 32 tokens in that operand order.
 //   - Scale and zero-point are per token, i.e. per row of S^T and per k-index of the second product: they are applied
 //     to four scores and eight probabilities per lane and block instead of to 2 x 128 code values per token.  The codes
-//     enter the matrix cores as 1024 + q (one byte permute per two codes); the bias and the zero-point leave through
-//     one fp32 term per query head.
+//     enter the matrix cores as 1024 + q (one byte permute per two codes; values of 8-bit codes as q); the bias of the keys
+//     and the zero-points leave through fp32 terms per query head, the bias of 4-bit values once per run of tokens.
 //   - The cache itself is stored in operand order (blocks of 32 tokens x 128 dimensions), the hardware-aware packing of
 //     the weights applied to K and V: every load instruction of a wave reads 1 KiB of consecutive bytes (row-major keys
 //     had every instruction touch half of sixteen 128-byte rows: 4.1 instead of 5.7 TB/s).
@@ -571,13 +571,12 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
         move_reference<PACK>(mx, st, acc);
         scores(st.m_run);
     }
-    // probability times the value scale of that token, rounded to fp16: the operand of the second product.  The correction
-    // term must be built from the very fp16 values the matrix core multiplies: the bias is about a
-    // thousand times the payload, so one fp16 ulp of disagreement on a single probability shifts a whole output row by
-    // several per cent.  Left to itself the compiler rounds p * vs once for the operand (fused multiply-and-convert)
-    // and once more, through fp32, for the sum below; the two differ when the fp32 product lands on an fp16 tie.
-    // Pinning the packed operand makes it the only copy.
-    float psum = 0.f, bsum = 0.f, zsum = 0.f;
+    // probability times the value scale of that token, rounded to fp16: the operand of the second product.  The zero-point
+    // term must be built from the very fp16 values the matrix core multiplies: a zero-point is as large as the codes and the
+    // two sums cancel, so a disagreement of one fp16 ulp per probability would stay in the result at full size.  Left to itself
+    // the compiler rounds p * vs once for the operand (fused multiply-and-convert) and once more, through fp32, for the sum
+    // below; the two differ when the fp32 product lands on an fp16 tie.  Pinning the packed operand makes it the only copy.
+    float psum = 0.f, zsum = 0.f;
     f16x8 pb[NH];
 #pragma unroll
     for (int n = 0; n < NH; ++n) {
@@ -594,12 +593,11 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
             own[j][0] = (uint32_t)__builtin_bit_cast(uint16_t, q[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[1]) << 16);
             own[j][1] = (uint32_t)__builtin_bit_cast(uint16_t, q[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[3]) << 16);
             asm volatile("" : "+v"(own[j][0]), "+v"(own[j][1]));
-            // sum over the lane's tokens of (bias + z) * p' - for 4-bit codes of z * p' only, see below
+            // sum over the lane's tokens of z * p'; the bias leaves below
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 const f16x2 two = as_f16x2(own[j][rr >> 1]);
                 const float pv = (float)(rr & 1 ? two.y : two.x);
-                if (BITS == 8) bsum = __builtin_fmaf(pv, 1.0f, bsum);
                 zsum = __builtin_fmaf((float)as_f16x2(vw[n][j][rr]).y, pv, zsum);
             }
         }
@@ -616,11 +614,12 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
         pb[n] = __builtin_bit_cast(f16x8, bits);
     }
     st.l_run += psum;
-    st.corr += __builtin_fmaf(1024.0f, bsum, zsum);
+    st.corr += zsum;
+    // The bias of a value code is several times the payload (4-bit codes: up to a hundred times): carried along to the end of
+    // a long context it would cost the sums their low bits, in proportion to the context.  8-bit codes lose it before the product
+    // (1024 + q - 1024 is exact).  For 4-bit codes, which bring half the bytes per instruction, one product with the constant operand -bias
+    // (1024, or 64 at the k-values 2, 3, 6 and 7 of a word) takes it out run by run, before the codes that carry it go in.
     if constexpr (BITS == 4) {
-        // The bias of a 4-bit value code is up to a hundred times the payload: carried along to the end of a long context it
-        // would cost the sums their low bits.  One product with the constant operand -bias (1024, or 64 at the k-values 2, 3, 6
-        // and 7 of a word) takes it out run by run, before the codes that carry it go in.
         const _Float16 a = (_Float16)-1024.0f, b = (_Float16)-64.0f;
         const f16x8 minus_bias = {a, a, b, b, a, a, b, b};
         f32x4 bias = {0.f, 0.f, 0.f, 0.f};
@@ -637,7 +636,7 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
             f16x8 a;
             if constexpr (BITS == 8) {
                 const u32x4 w = r.v[i >> 1];
-                a = (i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y);
+                a = ((i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y)) - (_Float16)1024.0f;
             } else {
                 a = biased8(r.v[2 * (N0 + n) + (i >> 2)][i & 3], mg);
             }
@@ -832,7 +831,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) sm_out[wave][i][rr][lane] = acc[i][rr] - corr_w;   // bias and zero-point leave here
+        for (int rr = 0; rr < 4; ++rr) sm_out[wave][i][rr][lane] = acc[i][rr] - corr_w;   // the zero-points leave here
     __syncthreads();
     // thread (wave w, lane) finalises row tiles 2w and 2w+1 of its column
     float M = kNegBig;

@@ -281,6 +281,40 @@ def test_attn_decode_splits(tm, B, Hkv, G, T, bound, bits):
     cache.close()
 
 
+@pytest.mark.parametrize("G", [4, 16])                       # both forms of the kernel: up to eight query heads per KV head, more
+@pytest.mark.parametrize("bits", [8, 4])
+def test_attn_decode_sums_of_a_long_context(tm, bits, G):
+    """Unsplit contexts of 32768 tokens (256 (sequence, head) pairs, one CTA each) with a zero query: every probability is
+    exactly one, so that the result is the mean of the dequantised values, up to the fp32 sums and the final rounding.  In units of
+    a value's scale: a wave adds up 8192 codes of 127 on average, so its sums end near 2^20, where an fp32 ulp is 1/16 (0.036 rms on the
+    way there).  256 products with, at four values a step, eight roundings of 0.29 ulp each make 0.47, the four waves 0.94; the
+    result before the division is 42 * sqrt(32768) = 7600: 1.2e-4 of it (4-bit codes: sums and result are both 17 times smaller).
+    Twice that is allowed.  Sums that carry a conversion bias of 1024 per token to the end are eight times as long: 1e-3."""
+    import torch
+    B, Hkv, T = 64, 4, 32768
+    _say(f"attn decode long sums bits={bits} G={G}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(bits + G)
+    V = torch.randn((T, Hkv, 128), generator=g, device="cuda").half()
+    cache = tm.tm_kv_create(B, Hkv, T, bits)
+    for t in range(0, T, 2048):
+        v = V[t:t + 2048].expand(B, 2048, Hkv, 128).contiguous()
+        tm.tm_kv_append(cache, v, v, torch.full((B,), t, dtype=torch.int32, device="cuda"))
+    Q = torch.zeros((B, Hkv * G, 128), dtype=torch.float16, device="cuda")
+    O = torch.full_like(Q, float("nan"))
+    tm.tm_attn_decode(Q, cache, torch.full((B,), T, dtype=torch.int32, device="cuda"), O, 128 ** -0.5, max_len=T)
+    torch.cuda.synchronize()
+    q, s, z = oa.kv_quantise(V.cpu().numpy().transpose(1, 0, 2)[None], bits)
+    ref = ((q[0].astype(np.float64) - z[0].astype(np.float64)[..., None]) * s[0].astype(np.float64)[..., None]).mean(1)     # [Hkv][128]
+    got = O.cpu().numpy().reshape(B, Hkv, G, 128).astype(np.float64)
+    rms = np.sqrt((ref ** 2).mean())
+    floor = np.sqrt(((ref.astype(np.float16).astype(np.float64) - ref) ** 2).mean())
+    err = np.sqrt(((got - ref[None, :, None]) ** 2).mean())
+    _say(f"  error {err / rms:.3e} of the result, fp16 rounding alone {floor / rms:.3e}")
+    assert err <= np.hypot(floor, 2.5e-4 * rms), (err / rms, floor / rms)
+    cache.close()
+
+
 def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
