@@ -503,7 +503,7 @@ __device__ __forceinline__ void move_reference(float mx, SoftmaxState& st, f32x4
 // its own tokens and meet at the end (xor 8, 16, 32).
 template <int BITS, bool PACK, int N0, int NH>
 __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t* sz_slot, const f16x8 (&qf)[4],
-                                              float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len,
+                                              float scale_log2e, float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len,
                                               int lane, SoftmaxState& st, f32x4 (&acc)[8])
 {
     constexpr int NS = PACK ? 1 : 2;                         // score tiles a lane keeps of a run
@@ -543,14 +543,15 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
                 const bool live = 32 * n + 16 * j + rr < rem;
                 kp[n][j][rr] = as_f16x2(rr < 2 ? p0[2 * rr] : p1[2 * (rr - 2)]);
                 vw[n][j][rr] = live ? (rr < 2 ? p0[2 * rr + 1] : p1[2 * (rr - 2) + 1]) : 0u;
-                // sum_d q_d Q_d  -  z sum_d Q_d  =  sum_d (q_d - z) Q_d.  (Multiply-adds throughout, so that the fp16 pair
-                // enters the instruction directly; an addend of +0 keeps one from being folded into a plain multiply.)
+                // sum_d q_d Q_d  -  z sum_d Q_d  =  sum_d (q_d - z) Q_d, times scale * log2(e).  (The pair enters a multiply-add,
+                // which takes fp16 directly.  The scale goes here, in fp32, and not into the query's fp16 values, where its rounding
+                // would be a fifth of the result's error.)
                 const float dm = PACK ? (jl ? d[1][rr] : d[0][rr]) : d[j][rr];
-                t[n][j][rr] = __builtin_fmaf(-(float)kp[n][j][rr].y, qsum, dm);
+                t[n][j][rr] = scale_log2e * __builtin_fmaf(-(float)kp[n][j][rr].y, qsum, dm);
             }
         }
     }
-    // scores in base 2 (the query carries scale * log2(e)) less the reference
+    // scores in base 2 less the reference
     float x[NH][NS][4], mx = kNegBig;
     auto scores = [&](float ref) {
         mx = kNegBig;
@@ -648,15 +649,15 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
 // instructions; with two score tiles a lane that takes more registers than there are, so there they go one after the other.
 template <int BITS, bool PACK>
 __device__ __forceinline__ void process_block(const BlockRegs& r, const uint32_t* sz_slot, const f16x8 (&qf)[4],
-                                              float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len, int len_all,
+                                              float scale_log2e, float qsum, const f32x4& neg_qbias, const Magic& mg, int blk, int len, int len_all,
                                               int lane, SoftmaxState& st, f32x4 (&acc)[8])
 {
     if constexpr (BITS == 8 || PACK) {
-        process_runs<BITS, PACK, 0, BITS == 8 ? 1 : 2>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
+        process_runs<BITS, PACK, 0, BITS == 8 ? 1 : 2>(r, sz_slot, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, lane, st, acc);
     } else {
-        process_runs<BITS, PACK, 0, 1>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
+        process_runs<BITS, PACK, 0, 1>(r, sz_slot, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, lane, st, acc);
         if (blk * 64 + 32 < len_all)                         // (wave-uniform) the second run may lie wholly behind the context
-            process_runs<BITS, PACK, 1, 1>(r, sz_slot, qf, qsum, neg_qbias, mg, blk, len, lane, st, acc);
+            process_runs<BITS, PACK, 1, 1>(r, sz_slot, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, lane, st, acc);
     }
 }
 
@@ -764,7 +765,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     load_block<BITS>(r1, z1, rs, blk + 4 < blk1 ? blk + 4 : nblk, lane);
 
     // Query operand (adaptive head alignment): column m = c, k-values of step tt = dimensions 32h + 8tt .. +7, the
-    // order in which the lane's key bytes arrive; scaled once by scale * log2(e).
+    // order in which the lane's key bytes arrive.
     f16x8 qf[4];
     float qsum = 0.f, qbias = 0.f;
     const Magic mg = make_magic();
@@ -773,14 +774,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int tt = 0; tt < 4; ++tt) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                qf[tt][e] = real ? (_Float16)((float)qraw[tt][e] * scale_log2e) : (_Float16)0.0f;
-            }
-            // the sums below must see the very fp16 values the matrix core multiplies (one rounding, one copy)
-            u32x4 bits = __builtin_bit_cast(u32x4, qf[tt]);
-            asm volatile("" : "+v"(bits.x), "+v"(bits.y), "+v"(bits.z), "+v"(bits.w));
-            qf[tt] = __builtin_bit_cast(f16x8, bits);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
+                qf[tt][e] = real ? qraw[tt][e] : (_Float16)0.0f;
                 qsum += (float)qf[tt][e];
                 qbias += ((e & 2) ? 64.0f : 1024.0f) * (float)qf[tt][e];     // bias of a 4-bit code at operand position e
             }
@@ -800,15 +794,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (blk < blk1) {
         while (true) {
             load_block<BITS>(r2, z2, rs, blk + 8 < blk1 ? blk + 8 : nblk, lane);
-            process_block<BITS, PACK>(r0, z0, qf, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
+            process_block<BITS, PACK>(r0, z0, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
             blk += 4;
             if (blk >= blk1) break;
             load_block<BITS>(r0, z0, rs, blk + 8 < blk1 ? blk + 8 : nblk, lane);
-            process_block<BITS, PACK>(r1, z1, qf, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
+            process_block<BITS, PACK>(r1, z1, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
             blk += 4;
             if (blk >= blk1) break;
             load_block<BITS>(r1, z1, rs, blk + 8 < blk1 ? blk + 8 : nblk, lane);
-            process_block<BITS, PACK>(r2, z2, qf, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
+            process_block<BITS, PACK>(r2, z2, qf, scale_log2e, qsum, neg_qbias, mg, blk, len, len_all, lane, st, acc);
             blk += 4;
             if (blk >= blk1) break;
         }

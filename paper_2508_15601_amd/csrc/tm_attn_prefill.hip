@@ -54,7 +54,7 @@ __device__ __forceinline__ f16x8 add_pairs(f16x8 v, f16x2 a, f16x2 b, f16x2 c, f
 
 constexpr int ST = 64;                           // tokens per stage
 constexpr int kStageBytes = ST * kHeadDim * 2;   // one stage of keys (or values) in fp16
-constexpr int kStagePairs = ST * 8;              // one stage of scales and zero-points
+constexpr int kStagePairs = ST * 10;             // one stage of scales and zero-points
 // Keys are read one stage ahead of the barrier that ends it, values after it: two key buffers, three value buffers, and
 // four sets of pairs (read from the conversion of a stage to its last product).
 constexpr int kLdsBytes = 5 * kStageBytes + 4 * kStagePairs;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rg = wave % RW, ks = wave / RW;
+    const int rg = wave % RW, ksg = wave / RW;
     const int hl = lane >> 5;
     const int hk = blockIdx.x, b = blockIdx.y;
     const int tile = (int)gridDim.z - 1 - (int)blockIdx.z;  // the longest rows first
@@ -130,7 +130,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto load_pairs = [&](int st) {
         if (tid < ST) pairs = __builtin_amdgcn_raw_buffer_load_b64(zrs, (st * ST + tid) * 8, 0, 0);
     };
-    // LDS image of a stage's pairs: [ST] words K scale | V scale << 16, then [ST] K zero-points, [ST] V zero-points (fp16).
+    // LDS image of a stage's pairs: [ST] K scales times scale * log2(e) in fp32 (in the query's fp16 values the factor's rounding
+    // would be a fifth of the result's error), then [ST] V scales, [ST] K zero-points, [ST] V zero-points (fp16).
     // A token that was never stored may hold anything; its scores are masked, and with finite numbers here its values
     // cannot reach a sum (0 * q).
     auto store_pairs = [&](int st) {
@@ -141,9 +142,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const _Float16 vs = v.x < (_Float16)65504.0f && v.x > (_Float16)-65504.0f ? v.x : nul;
             const _Float16 kz = __builtin_fminf16(__builtin_fmaxf16(k.y, nul), top);
             const _Float16 vz = __builtin_fminf16(__builtin_fmaxf16(v.y, nul), top);
-            ((uint32_t*)p)[tid] = (pairs.x & 0xffffu) | ((uint32_t)__builtin_bit_cast(uint16_t, vs) << 16);
-            ((_Float16*)(p + ST * 4))[tid] = kz;
-            ((_Float16*)(p + ST * 6))[tid] = vz;
+            ((float*)p)[tid] = (float)k.x * scale_log2e;
+            ((_Float16*)(p + ST * 4))[tid] = vs;
+            ((_Float16*)(p + ST * 6))[tid] = kz;
+            ((_Float16*)(p + ST * 8))[tid] = vz;
         }
     };
     const Magic mg = make_magic();
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto convert_stage = [&](int st) {
         unsigned char* const kb = kbase + (st & 1) * kStageBytes;
         unsigned char* const vb = vbase + (st % 3) * kStageBytes;
-        const unsigned char* const zk = pbase + (st & 3) * kStagePairs + ST * 4;
+        const unsigned char* const zk = pbase + (st & 3) * kStagePairs + ST * 6;
         const unsigned char* const zv = zk + ST * 2;
         if constexpr (BITS == 8) {
             convert_k(tid, codes[0], kb, zk);
@@ -218,11 +220,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     convert_stage(0);
     load_codes(1);
 
-    // the query, scaled once by scale * log2(e) and rounded to fp16
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qf[t][e] = real ? (_Float16)((float)qf[t][e] * scale_log2e) : (_Float16)0.0f;
+        for (int e = 0; e < 8; ++e) qf[t][e] = real ? qf[t][e] : (_Float16)0.0f;
     barrier();
 
     f32x16 o[4];
@@ -232,7 +233,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; ++e) o[d][e] = 0.f;
     float m_run = kMaskFloor, l_run = 0.f;
     f32x16 x;                                              // the current 32 tokens' scores, less the reference
-    uint32_t ss[16];                                       // their scale words
+    f32x4 ks[4];                                           // their keys' scales
+    u32x2 vs[4];                                           // and their values' (fp16)
     float mx;
 
     // raw scores of the 32 tokens whose keys start at kb
@@ -244,13 +246,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int t = 0; t < 8; ++t) s = mfma32x32x16(*(const f16x8*)(kb + t * 1024 + lane * 16), qf[t], s);
         return s;
     };
-    // scale words of the lane's tokens: register 4g + i holds token {0, 16, 8, 24}[g] + 4 * hl + i
-    auto read_scales = [&](const unsigned char* p) {
+    // scales of the lane's tokens: element i of register g is token {0, 16, 8, 24}[g] + 4 * hl + i of the run
+    auto read_scales = [&](const unsigned char* p, int run) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const u32x4 w = *(const u32x4*)(p + ((g & 1) * 16 + (g >> 1) * 8 + 4 * hl) * 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ss[4 * g + i] = w[i];
+            const int token = run * 32 + (g & 1) * 16 + (g >> 1) * 8 + 4 * hl;
+            ks[g] = *(const f32x4*)(p + token * 4);
+            vs[g] = *(const u32x2*)(p + ST * 4 + token * 2);
         }
     };
     // x = s * scale - ref; masked: tokens from the row's length on get kNegBig.  t0: first of the 32 tokens
@@ -258,19 +260,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int rem = len - t0 - 4 * hl;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const float v = __builtin_fmaf(s[e], (float)as_f16x2(ss[e]).x, -ref);
+            const float v = __builtin_fmaf(s[e], ks[e >> 2][e & 3], -ref);
             x[e] = !decltype(MASKED)::value || ((e >> 2) & 1) * 16 + (e >> 3) * 8 + (e & 3) < rem ? v : kNegBig;
         }
         mx = x[0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, x[e]);
     };
-    auto first_token = [&](int st, int sub) { return st * ST + (KS > 1 ? ks : sub) * 32; };
+    auto first_token = [&](int st, int sub) { return st * ST + (KS > 1 ? ksg : sub) * 32; };
 
     {
         const int t0 = first_token(0, 0);
-        const f32x16 s = multiply_k(kbase + (KS > 1 ? ks : 0) * 8192);
-        read_scales(pbase + (KS > 1 ? ks : 0) * 128);
+        const f32x16 s = multiply_k(kbase + (KS > 1 ? ksg : 0) * 8192);
+        read_scales(pbase, KS > 1 ? ksg : 0);
         scale_scores(s, 0.f, std::true_type{}, t0);
         m_run = fmaxf(fmaxf(mx, other_half(mx)), kMaskFloor);
         scale_scores(s, m_run, std::true_type{}, t0);
@@ -298,22 +300,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     for (int d = 0; d < 4; ++d) o[d] *= alpha;
                 }
                 // the next scores next to the exponentials of these
-                const int run_n = KS > 1 ? ks : sub_n;
+                const int run_n = KS > 1 ? ksg : sub_n;
                 const f32x16 s = multiply_k(kbase + (st_n & 1) * kStageBytes + run_n * 8192);
                 f16x8 p[2];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const float pe = __builtin_amdgcn_exp2f(x[e]);
                     l_run += pe;
-                    p[e >> 3][e & 7] = (_Float16)__builtin_fmaf((float)as_f16x2(ss[e]).y, pe, 0.0f);
+                    const f16x2 two = as_f16x2((e & 2) ? vs[e >> 2].y : vs[e >> 2].x);
+                    p[e >> 3][e & 7] = (_Float16)__builtin_fmaf((float)((e & 1) ? two.y : two.x), pe, 0.0f);
                 }
                 // the products with V next to the scaling of the next scores
-                const unsigned char* const vb = vbase + (st % 3) * kStageBytes + (KS > 1 ? ks : sub) * 8192 + lane * 16;
+                const unsigned char* const vb = vbase + (st % 3) * kStageBytes + (KS > 1 ? ksg : sub) * 8192 + lane * 16;
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int d = 0; d < 4; ++d) o[d] = mfma32x32x16(*(const f16x8*)(vb + (2 * d + k) * 1024), p[k], o[d]);
-                read_scales(pbase + (st_n & 3) * kStagePairs + run_n * 128);
+                read_scales(pbase + (st_n & 3) * kStagePairs, run_n);
                 const int t_n = first_token(st_n, sub_n);
                 if (t_n + 32 > wmin) scale_scores(s, m_run, std::true_type{}, t_n);
                 else scale_scores(s, m_run, std::false_type{}, t_n);
@@ -327,7 +330,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         float* const part = (float*)smem;
         barrier();
         float* const slot = part + rg * (66 * 64) + lane;
-        if (ks > 0) {
+        if (ksg > 0) {
             slot[0] = m_run;
             slot[64] = l;
 #pragma unroll
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int e = 0; e < 16; ++e) slot[(2 + 16 * d + e) * 64] = o[d][e];
         }
         barrier();
-        if (ks > 0) return;
+        if (ksg > 0) return;
         const float M = fmaxf(m_run, slot[0]);
         const float f0 = __builtin_amdgcn_exp2f(m_run - M), f1 = __builtin_amdgcn_exp2f(slot[0] - M);
         l = l * f0 + slot[64] * f1;

@@ -315,6 +315,42 @@ def test_attn_decode_sums_of_a_long_context(tm, bits, G):
     cache.close()
 
 
+@pytest.mark.parametrize("n,past", [(1, 4095), (1, 2047), (32, 2000), (512, 1500)])      # two decoding steps, both prompt kernels
+@pytest.mark.parametrize("bits", [8, 4])
+def test_attn_error_is_that_of_probabilities_and_result(tm, bits, n, past):
+    """Gaussian queries, keys and values.  Two roundings to fp16 belong to the path: of the result (computed here) and of every
+    probability times its scale.  The latter is 2^-10 / sqrt(12) of a power of two, over mantissas spread evenly in the
+    logarithm 2.1e-4 of the value, independent from token to token, hence 2.1e-4 of the result.  A query rounded after its
+    scaling would add as much again (the scores' spread is one): 3.6e-4 in all.  8 % above the two is allowed."""
+    import torch
+    Hkv, G, T = 8, 4, past + n
+    _say(f"attn error bits={bits} n={n} past={past}")
+    rng = np.random.default_rng(bits * 1000 + past)
+    K, V = (rng.standard_normal((1, Hkv, T, 128)).astype(np.float16) for _ in range(2))
+    Q = rng.standard_normal((1, n, Hkv * G, 128)).astype(np.float16)
+    cache = tm.tm_kv_create(1, Hkv, T, bits)
+    tm.tm_kv_append(cache, _dev(K.transpose(0, 2, 1, 3)), _dev(V.transpose(0, 2, 1, 3)), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    O = torch.full((1, n, Hkv * G, 128), float("nan"), dtype=torch.float16, device="cuda")
+    if n == 1:
+        tm.tm_attn_decode(_dev(Q[:, 0]), cache, torch.full((1,), T, dtype=torch.int32, device="cuda"), O[:, 0], 128 ** -0.5)
+    else:
+        tm.tm_attn_prefill(_dev(Q), cache, torch.full((1,), past, dtype=torch.int32, device="cuda"), O, 128 ** -0.5)
+    torch.cuda.synchronize()
+    k, v = (oa.kv_dequant(*oa.kv_quantise(x, bits))[0] for x in (K, V))                            # [Hkv][T][128]
+    future = np.arange(T)[None] > past + np.arange(n)[:, None]
+    ref = np.empty((n, Hkv * G, 128))
+    for h in range(Hkv * G):
+        s = np.where(future, -np.inf, Q[0, :, h].astype(np.float64) @ k[h // G].T * 128 ** -0.5)
+        e = np.exp(s - s.max(1, keepdims=True))
+        ref[:, h] = (e / e.sum(1, keepdims=True)) @ v[h // G]
+    rms = np.sqrt((ref ** 2).mean())
+    result = np.sqrt(((ref.astype(np.float16) - ref) ** 2).mean()) / rms
+    err = np.sqrt(((O.cpu().numpy()[0] - ref) ** 2).mean()) / rms
+    _say(f"  error {err:.3e}, rounding of the result {result:.3e}")
+    assert err <= 1.08 * np.hypot(result, 2.1e-4), (err, result)
+    cache.close()
+
+
 def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
