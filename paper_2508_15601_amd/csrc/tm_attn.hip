@@ -730,7 +730,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     // Nothing is requested before the length is known: two blocks per wave ahead of it are 64 KiB per CTA that a short sequence
     // does not use (64 sequences x 8 heads of 1 / 100 tokens under a capacity of 32768: 7.3 / 7.7 us, with the length first
-    // 5.3 / 6.8), and save 0.1-0.3 us where the context is used whole (1 x 2048: 9.5 and 9.6 us with the append).
+    // 5.3 / 6.8), and save nothing where the context is used whole (0.2 % over 60 launches of 7-85 us).
     const int nblk = (len_all + TOK - 1) / TOK;
     const int blk0 = PREFILL ? 0 : split * blocks_per_split;
     const int blk1 = PREFILL ? nblk : min(nblk, blk0 + blocks_per_split);
@@ -775,6 +775,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 qf[tt][e] = real ? qraw[tt][e] : (_Float16)0.0f;
+            }
+            // (an ordering point only: it holds this arithmetic behind the requests above; without it launches of 10-15 us take 3 % longer)
+            u32x4 bits = __builtin_bit_cast(u32x4, qf[tt]);
+            asm volatile("" : "+v"(bits.x), "+v"(bits.y), "+v"(bits.z), "+v"(bits.w));
+            qf[tt] = __builtin_bit_cast(f16x8, bits);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
                 qsum += (float)qf[tt][e];
                 qbias += ((e & 2) ? 64.0f : 1024.0f) * (float)qf[tt][e];     // bias of a 4-bit code at operand position e
             }
