@@ -96,6 +96,13 @@ TM_API int tm_attn_decode(const uint16_t* Q, const tm_kv_cache* cache, const int
 TM_API int tm_attn_prefill(const uint16_t* Q, const tm_kv_cache* cache, const int32_t* positions, const int32_t* counts,
                            int count, uint16_t* O, int q_heads, float scale, tm_stream stream);
 
+/*
+ * Query hook: the form an attention call on this cache takes.  count = 0: a decoding step with this max_len, *splits = pieces
+ * every context is cut into, *rows = 0.  count > 0: a prompt chunk of that many tokens, *splits = 1, *rows = query rows per
+ * CTA (128 or 256; 0 = the kernel that takes 16).  Either out-pointer may be NULL.
+ */
+TM_API int tm_get_attn_plan(const tm_kv_cache* cache, int q_heads, int count, int max_len, int* splits, int* rows);
+
 /* Test hook: the cache's device buffers and sizes (host out-pointers, any may be NULL); memory stays owned by the cache. */
 TM_API int tm_kv_raw(const tm_kv_cache* cache, void** k_codes, void** v_codes, void** pairs, size_t* code_bytes,
                      size_t* pair_bytes);

@@ -60,6 +60,8 @@ def load_library():
     lib.tm_attn_decode.argtypes = [vp, vp, vp, vp, i, ctypes.c_float, i, vp]
     lib.tm_attn_prefill.restype = i
     lib.tm_attn_prefill.argtypes = [vp, vp, vp, vp, i, vp, i, ctypes.c_float, vp]
+    lib.tm_get_attn_plan.restype = i
+    lib.tm_get_attn_plan.argtypes = [vp, i, i, i, c.POINTER(i), c.POINTER(i)]
     lib.tm_kv_raw.restype = i
     lib.tm_kv_raw.argtypes = [vp, vp, vp, vp, vp, vp]
     lib.tm_pack_w4_actorder.restype = vp
@@ -524,6 +526,13 @@ def tm_attn_prefill(Q, cache: KvCache, positions, O, scale: float, counts=None, 
     """Causal attention of a chunk of prompt tokens over the cache: Q, O fp16 [batch][count][q_heads][128] device tensors,
     positions int32 [batch], counts int32 [batch] or None (see include/tm_attn.h)."""
     return (_calls or _native()).attn_prefill(Q, cache, positions, O, scale, counts, stream)
+
+
+def tm_get_attn_plan(cache: KvCache, q_heads: int, count: int = 0, max_len: int = 0):
+    """(splits, rows) of a decoding step (count = 0) or a prompt chunk, see include/tm_attn.h."""
+    splits, rows = ctypes.c_int(), ctypes.c_int()
+    _check(load_library().tm_get_attn_plan(cache.handle, q_heads, count, max_len, ctypes.byref(splits), ctypes.byref(rows)))
+    return splits.value, rows.value
 
 
 def tm_kv_raw(cache: KvCache):

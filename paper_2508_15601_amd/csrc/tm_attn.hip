@@ -1024,19 +1024,36 @@ hipError_t launch_kv_append(const AttnCache& kv, const uint16_t* Kn, const uint1
     return hipGetLastError();
 }
 
-hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int32_t* lens, uint16_t* O, int q_heads,
-                              float scale, int max_len, int num_cu, hipStream_t stream)
+// Pieces the context of every (sequence, KV head) is cut into at a decoding step; max_len <= 0: the capacity.
+int attn_decode_splits(const AttnCache& kv, int max_len, int num_cu, int* blocks_per_split)
 {
     const int tok = 256 / kv.bits;                                   // tokens per 4 KiB block
+    if (max_len <= 0 || max_len > kv.cap) max_len = kv.cap;
     const int nblk = (max_len + tok - 1) / tok;
     // One CTA per CU.  A CU streams its share as fast with one CTA as with two, and what a launch waits for is the CU with
     // the most: a second, partial round of CTAs (or lengths that leave two long ones on one CU) costs more than idle CUs do.  4-bit cache, 32
     // sequences of 4096-8192 tokens, 8 heads: 44.7 us in two splits, 39.5 unsplit; 8-bit, 27 x 4 heads, 10-20 thousand tokens:
-    // 85 us in five, 72 in two; 109 x 4 heads, 500-1000 tokens: 21.8 in two, 14.3 unsplit.  Only where that would leave almost half the CUs
-    // idle over a long context (129 ... 140 (sequence, head) pairs) the launch has two CTAs per CU instead.
+    // 85 us in five, 72 in two; 109 x 4 heads, 500-1000 tokens: 21.8 in two, 14.3 unsplit.  About 170 CTAs are enough for
+    // the memory rate that 256 reach (4-bit, 16384 tokens: 176 pairs 66 us, 256 pairs 90).
     const int segs = kv.batch * kv.heads;
     int splits = segs >= num_cu ? 1 : num_cu / segs;
-    if (segs > num_cu / 2 && segs * 20 <= num_cu * 11 && nblk >= 128) splits = (2 * num_cu + segs - 1) / segs;
+    // Two CTAs per CU (rounded up) over long contexts where one per CU leaves the most to a few of them (kv4/8 = bits of the codes,
+    // equal lengths / lengths between half and all, us):
+    //   just over half the CUs                  1 split        3              4              5
+    //     136 pairs x 8192, kv4              34.7 / 32.9    31.7 / 30.6    35.6 / 27.1    32.0 / 29.4
+    //     144 pairs x 8192, kv8              54.5 / 47.5    51.3 / 47.7    56.9 / 43.6    52.6 / 49.6
+    //     144 pairs x 4096, kv8              29.0 / 26.9    28.6 / 27.2    32.7 / 27.6    29.8 / 27.4
+    //     160 pairs x 8192, kv8              54.9 / 47.7    55.5 / 51.0    60.2 / 54.3    63.8 / 50.9
+    //   a few pairs more than CUs               1 split        2
+    //     272 pairs x 8192, kv4              70.4 / 51.8    62.9 / 45.5
+    //     320 pairs x 8192, kv8             119.4 / 100     112.7 / 92.9
+    //     352 pairs x 8192, kv4              71.7 / 61.2    68.2 / 62.5
+    //     272 pairs x 2048, kv8              32.3 / 27.9    31.3 / 25.5   (304 pairs: 32.9 / 28.4, 32.5 / 30.5)
+    const bool half = segs * 2 > num_cu && segs * 16 <= num_cu * 9 && max_len >= 8192;
+    const bool few_over = segs > num_cu && segs * 4 <= num_cu * 5 && nblk >= 128;
+    if (half || few_over) splits = (2 * num_cu + segs - 1) / segs;
+    // (Cutting more finely where max_len is only the capacity does not pay: 4 x 8 heads, capacity 32768, in 8 / 16 splits:
+    // 1000 tokens 11.3 / 12.2 us, 4000 tokens 24.7 / 17.9, all 32768 26 / 29.)
     // at least four blocks per wave and split (short contexts: up to eight splits of at least two - a 2048-token context
     // is cut in four or eight instead of two or four pieces, which shortens each CTA's serial chain more than the merge
     // costs; none below 24 blocks, where it costs more: 17 blocks 6.0 us unsplit, 7.1 in two), and no more partial results
@@ -1046,7 +1063,15 @@ hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int3
     if (splits > by_work) splits = by_work;
     if (splits > kv.max_splits) splits = kv.max_splits;
     const int bps = (nblk + splits - 1) / splits;
-    splits = (nblk + bps - 1) / bps > 0 ? (nblk + bps - 1) / bps : 1;
+    *blocks_per_split = bps;
+    return (nblk + bps - 1) / bps;
+}
+
+hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int32_t* lens, uint16_t* O, int q_heads,
+                              float scale, int max_len, int num_cu, hipStream_t stream)
+{
+    int bps;
+    const int splits = attn_decode_splits(kv, max_len, num_cu, &bps);
     if (kv.heads > 65535 || kv.batch > 65535) return hipErrorInvalidValue;
     const float scale_log2e = scale * 1.4426950408889634f;
     // up to sixteen splits are merged by the CTA that finishes last, eight loads in flight at once (two splits:

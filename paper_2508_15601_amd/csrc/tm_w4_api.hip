@@ -1724,7 +1724,6 @@ int tm_attn_decode(const uint16_t* Q, const tm_kv_cache* cache, const int32_t* l
     if (q_heads <= 0 || q_heads % hk || q_heads / hk > 128)
         return fail(TM_EINVAL, "q_heads = %d must be 1..128 times the cache's %d heads", q_heads, hk);
     if (!(scale > 0.0f) || !(scale < 1.0e6f)) return fail(TM_EINVAL, "scale out of range");
-    if (max_len <= 0 || max_len > cache->kv.cap) max_len = cache->kv.cap;
     int dev;
     int rc = check_device(&dev);
     if (rc != TM_OK) return rc;
@@ -1755,6 +1754,19 @@ int tm_attn_prefill(const uint16_t* Q, const tm_kv_cache* cache, const int32_t* 
     hipError_t e = launch_attn_prefill(cache->kv, Q, positions, counts, count, O, q_heads, scale, g_dev[dev].num_cu,
                                        (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "attention launch");
+    return TM_OK;
+}
+
+int tm_get_attn_plan(const tm_kv_cache* cache, int q_heads, int count, int max_len, int* splits, int* rows)
+{
+    if (!valid_kv(cache)) return fail(TM_EINVAL, "cache handle is null or invalid");
+    const int hk = cache->kv.heads;
+    if (q_heads <= 0 || q_heads % hk || q_heads / hk > 128 || count < 0)
+        return fail(TM_EINVAL, "q_heads = %d must be 1..128 times the cache's %d heads, count = %d not negative", q_heads, hk, count);
+    const int num_cu = g_dev[cache->device].num_cu;
+    int bps;
+    if (splits) *splits = count ? 1 : attn_decode_splits(cache->kv, max_len, num_cu, &bps);
+    if (rows) *rows = count ? attn_prefill_rows(cache->kv, count, q_heads, num_cu) : 0;
     return TM_OK;
 }
 

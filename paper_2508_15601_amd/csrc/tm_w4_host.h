@@ -99,6 +99,7 @@ hipError_t launch_kv_append(const AttnCache& kv, const uint16_t* Kn, const uint1
                             int count, hipStream_t stream);
 hipError_t launch_attn_decode(const AttnCache& kv, const uint16_t* Q, const int32_t* lens, uint16_t* O, int q_heads,
                               float scale, int max_len, int num_cu, hipStream_t stream);
+int attn_decode_splits(const AttnCache& kv, int max_len, int num_cu, int* blocks_per_split);
 hipError_t launch_attn_prefill(const AttnCache& kv, const uint16_t* Q, const int32_t* positions, const int32_t* counts,
                                int count, uint16_t* O, int q_heads, float scale, int num_cu, hipStream_t stream);
 hipError_t attn_prefill_setup();                                       // once per device, outside any capture

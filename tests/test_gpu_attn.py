@@ -351,6 +351,23 @@ def test_attn_error_is_that_of_probabilities_and_result(tm, bits, n, past):
     cache.close()
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,Hkv,G,T,bound,splits", [
+    (2, 72, 1, 8192, 8192, 4),       # just over half as many pairs as CUs, long contexts: two CTAs per CU
+    (4, 72, 1, 8192, 8192, 2),       # a few pairs more than CUs
+    (2, 80, 1, 8192, 8192, 1),       # between the two, and far above: one CTA per pair
+    (5, 66, 9, 2048, 2048, 1),
+    (4, 8, 2, 8192, 0, 8),           # fewer: cut into as many pieces as give one CTA per CU
+    (1, 16, 2, 16384, 16384, 16),
+])
+def test_attn_decode_split_rule(tm, B, Hkv, G, T, bound, splits, bits):
+    """How many pieces a context is cut into on 256 CUs, and that launches with as many are right."""
+    cache = tm.tm_kv_create(B, Hkv, T, bits)
+    assert tm.tm_get_attn_plan(cache, Hkv * G, max_len=bound) == (splits, 0)
+    cache.close()
+    test_attn_decode_splits(tm, B, Hkv, G, T, bound, bits)
+
+
 def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
