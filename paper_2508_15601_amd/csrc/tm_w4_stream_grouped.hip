@@ -76,7 +76,9 @@ hipError_t stream_grouped_setup()
 // eight (up to 4096).  `rows`: rows of an expert to size for; active: experts that can have rows.  A wave takes a quarter (an
 // eighth) of the K units and as many column tiles as keep its weights in flight to 64 registers - with four waves 48: two tiles
 // of four units ran 20 % faster than three - and the launch at two CTAs per CU.  LDS is sized for sixteen rows where sixteen waves'
-// share allows it, else for eight (an expert with more streams its weights again), else the form is not taken.
+// share allows it, else for eight (an expert with more takes a second pass), else the form is not taken.  Eight waves with groups of
+// 64 do not pay: 128 experts of 4096 x 3072, 16 / 64 tokens x 8: 120 / 183 us, 109 / 160 on the large CTAs (groups of 128: 104 / 157
+// and 124 / 170; of 32: 132 / 205 and 162 / 229).
 bool stream_grouped_form(int NT, int KU, int group, int active, double rows, int num_cu, Plan* one, int* pass_log, int* lds)
 {
     const int gpu = 128 / group;
@@ -88,7 +90,7 @@ bool stream_grouped_form(int NT, int KU, int group, int active, double rows, int
     ntw = ntw > 4 ? 4 : ntw;
     if (waves == 4 && ntw > 3) ntw = 3;
     while (ntw > 1 && (long)active * ((NT + ntw - 1) / ntw) < 2 * num_cu) --ntw;
-    if (ntw < 1 || !grouped_built(ntw, gpu, ni, waves)) return false;
+    if (ntw < 1 || !grouped_small_built(ntw, gpu, ni, waves)) return false;
     const size_t share = 160 * 1024 / (16 / waves) - 512;  // of the CU's LDS, for one of the resident CTAs
     for (int log = 4; log >= 3; --log) {
         int red_off;

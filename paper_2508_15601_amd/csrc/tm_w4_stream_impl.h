@@ -109,10 +109,10 @@ __device__ __forceinline__ void stream_reduce(const GemmParams& p, const f32x4 (
 }
 
 // One CTA: column tiles nt0 .. nt0 + NTW - 1, K slice sk.  smem: the waves' X regions, then (or later in the same
-// place, see red_off) the reduction tiles.
-template <int NTW, int GPU, int NI, int WAVES>
+// place, see red_off) the reduction tiles.  AGAIN: more rows for the weights that a first call has left in st.
+template <int NTW, int GPU, int NI, int WAVES, bool AGAIN = false>
 __device__ __forceinline__ void stream_body(const GemmParams& p, const int strip, const int sk, const int nt0,
-                                            unsigned char* __restrict__ smem, uint32_t& s_last)
+                                            unsigned char* __restrict__ smem, uint32_t& s_last, StreamRegs<NTW, GPU, NI>& st)
 {
     constexpr int GU = GPU;                        // K-groups per 128-row unit
     constexpr int TG = 4 / GU;                     // MFMA k-steps per K-group
@@ -160,8 +160,7 @@ __device__ __forceinline__ void stream_body(const GemmParams& p, const int strip
     __builtin_amdgcn_sched_barrier(0);             // the count in the wait below is exact only if nothing moves across
 
     // ---- every weight load of this wave, in the order of use
-    StreamRegs<NTW, GU, NI> st;
-    {
+    if constexpr (!AGAIN) {
         const uint32_t w_lane = (uint32_t)lane * 16u, s_lane = (uint32_t)c * 4u;
         const char* wbase = (const char*)p.W + (size_t)nt0 * p.KU * 1024;
         const char* sbase = (const char*)p.SZ + (size_t)nt0 * p.G * 64;
@@ -182,11 +181,22 @@ __device__ __forceinline__ void stream_body(const GemmParams& p, const int strip
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    {
+    if constexpr (!AGAIN) {
         // the X loads are older than the NI * NTW * (GU + 1) loads just issued: wait until at most that many are
         // outstanding (the counter field holds up to 63; a smaller bound only waits for a few weight loads as well)
         constexpr int kYounger = NI * NTW * (GU + 1) < 63 ? NI * NTW * (GU + 1) : 63;
         __builtin_amdgcn_s_waitcnt((kYounger & 15) | ((kYounger >> 4) << 14) | (7 << 4) | (15 << 8));
+    } else {
+        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));          // nothing but these loads (and stores) is in flight
+        // the weights stay packed: left alone the compiler keeps their fp16 values from call to call, in scratch memory
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NTW; ++j) {
+                asm volatile("" : "+v"(st.wq[i][j].x), "+v"(st.wq[i][j].y), "+v"(st.wq[i][j].z), "+v"(st.wq[i][j].w));
+#pragma unroll
+                for (int g = 0; g < GU; ++g) asm volatile("" : "+v"(st.sz[i][j][g]));
+            }
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -274,26 +284,33 @@ __global__ __launch_bounds__(MAXW * 64) void stream_kernel(GemmParams p)
     const int nt0 = strip * p.strip_base + min(strip, p.strip_rem);
     if constexpr (NTW > 1) {
         if (strip >= p.strip_rem && p.strip_base < NTW) {          // CTA-uniform
-            stream_body<NTW - 1, GPU, NI, MAXW>(p, strip, sk, nt0, stream_smem, s_last);
+            StreamRegs<NTW - 1, GPU, NI> st;
+            stream_body<NTW - 1, GPU, NI, MAXW>(p, strip, sk, nt0, stream_smem, s_last, st);
             return;
         }
     }
-    stream_body<NTW, GPU, NI, MAXW>(p, strip, sk, nt0, stream_smem, s_last);
+    StreamRegs<NTW, GPU, NI> st;
+    stream_body<NTW, GPU, NI, MAXW>(p, strip, sk, nt0, stream_smem, s_last, st);
 }
 
 // Grouped (mixture-of-experts) form of the one-shot kernels: blockIdx.y selects among the experts that have rows, as in
-// skinny_grouped_kernel; an expert's rows are taken pass_rows at a time, each pass a one-shot GEMM of its own (so the form
-// is meant for decode batches, where an expert seldom has more).  The LDS of the launch is sized for that many rows; the
-// reduction tiles lie behind the X regions of the pass where both fit.
-//
-// Many CTAs run one after the other on a CU here, each with a beginning (requests, first bytes) and an end (the sum over the
-// waves) that stream nothing.  So the CTAs are kept small enough for several to be resident - while one begins or ends, the
-// others stream: up to 64 registers of weights in flight per lane and 160 KiB of LDS for sixteen waves (two CTAs of eight or
-// four of four).  128 experts of 4096 x 3072 and 1536 x 4096 of which 82 have one or two rows: 117 -> 94-100 us on CTAs of eight
-// waves and three column tiles instead of eight, 72 -> 51 us (5.4 TB/s) on four waves and three tiles instead of sixteen and eight.
+// skinny_grouped_kernel; an expert's rows are taken sixteen at a time, each pass a one-shot GEMM of its own (so the form
+// is meant for decode batches, where an expert seldom has more than sixteen rows).  The LDS of the launch is sized for
+// sixteen rows; the reduction tiles lie behind the X regions of the pass where both fit.
+template <int NTW, int NI, int MAXW>
+__device__ __forceinline__ void grouped_rows(const GroupedParams& gp, GemmParams& p, int m0, int rows)
+{
+    p.X = gp.X + (size_t)m0 * gp.K;
+    p.Y = gp.Y + (size_t)m0 * p.ldy;
+    p.M = rows;
+    p.mp_log = p.M > 8 ? 4 : p.M > 4 ? 3 : p.M > 2 ? 2 : p.M > 1 ? 1 : 0;
+    const int x_bytes = ((((NI << p.mp_log) + 3) >> 2) << 10) * MAXW;
+    const int red_bytes = MAXW * NTW * 4 * 64 * (int)sizeof(float);
+    p.red_off = x_bytes + red_bytes <= gp.lds_bytes ? x_bytes : 0;
+}
+
 template <int NTW, int GPU, int NI, int MAXW>
-__global__ __launch_bounds__(MAXW * 64) __attribute__((amdgpu_waves_per_eu(NTW * NI * (4 + GPU) <= 64 ? 4 : 2))) void stream_grouped_kernel(
-    GroupedParams gp)
+__global__ __launch_bounds__(MAXW * 64) void stream_grouped_kernel(GroupedParams gp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
     __shared__ uint32_t s_last;
@@ -303,23 +320,69 @@ __global__ __launch_bounds__(MAXW * 64) __attribute__((amdgpu_waves_per_eu(NTW *
     const int strip = blockIdx.x;
     const int nt0 = strip * gp.strip_base + min(strip, gp.strip_rem);
     const bool narrow = NTW > 1 && strip >= gp.strip_rem && gp.strip_base < NTW;      // CTA-uniform
-    for (int m0 = er.r0; m0 < er.r1; m0 += gp.pass_rows) {
+    for (int m0 = er.r0; m0 < er.r1; m0 += 16) {
         if (m0 != er.r0) __syncthreads();           // the previous pass is done with LDS
-        p.X = gp.X + (size_t)m0 * gp.K;
-        p.Y = gp.Y + (size_t)m0 * p.ldy;
-        p.M = min(gp.pass_rows, er.r1 - m0);
-        p.mp_log = p.M > 8 ? 4 : p.M > 4 ? 3 : p.M > 2 ? 2 : p.M > 1 ? 1 : 0;
-        const int x_bytes = ((((NI << p.mp_log) + 3) >> 2) << 10) * MAXW;
-        const int red_bytes = MAXW * NTW * 4 * 64 * (int)sizeof(float);
-        p.red_off = x_bytes + red_bytes <= gp.lds_bytes ? x_bytes : 0;
+        grouped_rows<NTW, NI, MAXW>(gp, p, m0, min(16, er.r1 - m0));
         if constexpr (NTW > 1) {
             if (narrow) {
-                stream_body<NTW - 1, GPU, NI, MAXW>(p, strip, 0, nt0, stream_smem, s_last);
+                StreamRegs<NTW - 1, GPU, NI> st;
+                stream_body<NTW - 1, GPU, NI, MAXW>(p, strip, 0, nt0, stream_smem, s_last, st);
                 continue;
             }
         }
-        stream_body<NTW, GPU, NI, MAXW>(p, strip, 0, nt0, stream_smem, s_last);
+        StreamRegs<NTW, GPU, NI> st;
+        stream_body<NTW, GPU, NI, MAXW>(p, strip, 0, nt0, stream_smem, s_last, st);
     }
+}
+
+// The same on small CTAs, for launches whose experts have few rows.  Many CTAs run one after the other on a CU then, each with a
+// beginning (requests, first bytes) and an end (the sum over the waves) that stream nothing.  So they are kept small enough for
+// several to be resident - while one begins or ends, the others stream: up to 64 registers of weights in flight per lane and
+// 160 KiB of LDS for sixteen waves (two CTAs of eight or four of four).  128 experts of 4096 x 3072 and 1536 x 4096 of which 82
+// have one or two rows: 117 -> 94-100 us on CTAs of eight waves and three column tiles instead of eight, 72 -> 51 us (5.4 TB/s) on
+// four waves and three tiles instead of sixteen and eight.
+//
+// That LDS holds eight rows of a long K, and who has how many rows is known on the device only.  An expert with more than a pass
+// takes keeps its weights in registers for the later passes (64 tokens x 8 of 128 experts, one of which has 55 rows, groups of
+// 32: 301 us with the weights read again for every pass, 273 like this, 301 on the large CTAs).  That is code of its own: kept over a
+// loop, the weights cost registers that the single pass does not have to spare.  What remains: the more CTAs, the more often X is
+// read, so where all tokens take the same few experts, sixteen rows each, the large CTAs are 10-28 % faster.
+template <int NTW, int GPU, int NI, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) __attribute__((amdgpu_waves_per_eu(4))) void stream_grouped_small_kernel(GroupedParams gp)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
+    __shared__ uint32_t s_last;
+    const ExpertRows er = find_expert(gp, blockIdx.y, threadIdx.x & 63);
+    if (!er.found) return;
+    GemmParams p = expert_params(gp, er);
+    const int strip = blockIdx.x;
+    const int nt0 = strip * gp.strip_base + min(strip, gp.strip_rem);
+    const bool narrow = NTW > 1 && strip >= gp.strip_rem && gp.strip_base < NTW;      // CTA-uniform
+    const int pass = gp.pass_rows;
+    auto run = [&](auto W, auto MORE) {
+        constexpr int kW = decltype(W)::value;
+        StreamRegs<kW, GPU, NI> st;
+        grouped_rows<NTW, NI, MAXW>(gp, p, er.r0, min(pass, er.r1 - er.r0));
+        stream_body<kW, GPU, NI, MAXW>(p, strip, 0, nt0, stream_smem, s_last, st);
+        if constexpr (decltype(MORE)::value) {
+            for (int m0 = er.r0 + pass; m0 < er.r1; m0 += pass) {
+                __syncthreads();                    // the previous pass is done with LDS
+                grouped_rows<NTW, NI, MAXW>(gp, p, m0, min(pass, er.r1 - m0));
+                stream_body<kW, GPU, NI, MAXW, true>(p, strip, 0, nt0, stream_smem, s_last, st);
+            }
+        }
+    };
+    auto run_width = [&](auto MORE) {
+        if constexpr (NTW > 1) {
+            if (narrow) {
+                run(std::integral_constant<int, NTW - 1>{}, MORE);
+                return;
+            }
+        }
+        run(std::integral_constant<int, NTW>{}, MORE);
+    };
+    if (er.r1 - er.r0 <= pass) run_width(std::false_type{});
+    else run_width(std::true_type{});
 }
 
 // LDS layout of a launch: the waves' X regions (whole 1 KiB load instructions each), and the waves' reduction tiles
@@ -372,21 +435,30 @@ hipError_t stream_raise_one()
     }
 }
 
-// The grouped form is built for CTAs of four waves too, and for CTAs of eight with few weights in flight: narrow strips only.
-constexpr bool grouped_built(int ntw, int gpu, int ni, int maxw)
+// The grouped form on small CTAs: four waves, or eight with few weights in flight; narrow strips only.
+constexpr bool grouped_small_built(int ntw, int gpu, int ni, int maxw)
 {
     const int inflight = ni * ntw * (4 + gpu);
     if (maxw == 4) return ntw <= 3 && ni <= 4 && inflight <= 48;
-    return stream_built(ntw, gpu, ni, maxw) || (maxw == 8 && ntw <= 4 && inflight <= 64);
+    return maxw == 8 && gpu != 2 && ntw <= 4 && (ni == 3 || ni == 4) && inflight <= 64;
+}
+
+template <int NTW, int GPU, int NI, int MAXW>
+constexpr auto grouped_kernel() -> void (*)(GroupedParams)
+{
+    if constexpr (grouped_small_built(NTW, GPU, NI, MAXW)) return &stream_grouped_small_kernel<NTW, GPU, NI, MAXW>;
+    else if constexpr (MAXW > 4 && stream_built(NTW, GPU, NI, MAXW)) return &stream_grouped_kernel<NTW, GPU, NI, MAXW>;
+    else return nullptr;
 }
 
 template <int NTW, int GPU, int NI, int MAXW>
 hipError_t launch_stream_grouped_one(const GroupedParams& gp, int experts, int block, hipStream_t stream)
 {
-    if constexpr (grouped_built(NTW, GPU, NI, MAXW)) {
+    constexpr auto kernel = grouped_kernel<NTW, GPU, NI, MAXW>();
+    if constexpr (kernel != nullptr) {
         dim3 grid(gp.strips, gp.total_rows < experts ? gp.total_rows : experts);
         if (block != MAXW * 64) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((stream_grouped_kernel<NTW, GPU, NI, MAXW>), grid, dim3(block), gp.lds_bytes, stream, gp);
+        hipLaunchKernelGGL(kernel, grid, dim3(block), gp.lds_bytes, stream, gp);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;
@@ -396,8 +468,9 @@ hipError_t launch_stream_grouped_one(const GroupedParams& gp, int experts, int b
 template <int NTW, int GPU, int NI, int MAXW>
 hipError_t stream_grouped_raise_one()
 {
-    if constexpr (grouped_built(NTW, GPU, NI, MAXW)) {
-        return hipFuncSetAttribute((const void*)stream_grouped_kernel<NTW, GPU, NI, MAXW>,
+    constexpr auto kernel = grouped_kernel<NTW, GPU, NI, MAXW>();
+    if constexpr (kernel != nullptr) {
+        return hipFuncSetAttribute((const void*)kernel,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStreamLdsBudget);
     } else {
         return hipSuccess;
