@@ -253,8 +253,10 @@ TM_API int tm_gemm_w4a16_grouped(const uint16_t* X, const tm_expert_group* group
  */
 TM_API int tm_gemm_w4a16_grouped_act(const uint16_t* X, const tm_expert_group* group, const int32_t* offsets, uint16_t* Y,
                                      int total_rows, int act, tm_stream stream);
-/* Kernel variant and strips per expert the grouped launch would use (host out-pointers, may be NULL). */
+/* Kernel variant and strips per expert the grouped launch uses (host out-pointers, may be NULL). */
 TM_API int tm_get_grouped_plan(const tm_expert_group* group, int total_rows, int* variant, int* strips);
+/* The same, with the CTA size and the rows of an expert taken at a time where the launch is a one-shot decode kernel's (else 0). */
+TM_API int tm_get_grouped_form(const tm_expert_group* group, int total_rows, int* variant, int* strips, int* threads, int* pass_rows);
 
 /* Shape of a handle; any out-pointer (host) may be NULL.  `bytes` = device bytes held (weights + scale/zero pairs). */
 TM_API int tm_packed_info(const tm_packed_w4* packed, int* K, int* N, int* group, size_t* bytes);

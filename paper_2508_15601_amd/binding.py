@@ -80,6 +80,8 @@ def load_library():
     lib.tm_gemm_w4a16_grouped.argtypes = [vp, vp, vp, vp, i, vp]
     lib.tm_gemm_w4a16_grouped_act.restype = i
     lib.tm_gemm_w4a16_grouped_act.argtypes = [vp, vp, vp, vp, i, i, vp]
+    lib.tm_get_grouped_form.restype = i
+    lib.tm_get_grouped_form.argtypes = [vp, i, vp, vp, vp, vp]
     lib.tm_get_grouped_plan.restype = i
     lib.tm_get_grouped_plan.argtypes = [vp, i, vp, vp]
     lib.tm_pack_w4_layout.restype = vp
@@ -335,6 +337,13 @@ def tm_get_grouped_plan(group: ExpertGroup, total_rows: int):
     v, st = ctypes.c_int(), ctypes.c_int()
     _check(load_library().tm_get_grouped_plan(group.handle, total_rows, ctypes.byref(v), ctypes.byref(st)))
     return v.value, st.value
+
+
+def tm_get_grouped_form(group: ExpertGroup, total_rows: int):
+    """(variant, strips, threads, pass_rows) of the grouped launch, see include/tm_w4.h."""
+    out = [ctypes.c_int() for _ in range(4)]
+    _check(load_library().tm_get_grouped_form(group.handle, total_rows, *map(ctypes.byref, out)))
+    return tuple(v.value for v in out)
 
 
 def tm_gemm_w4a16(X, packed: PackedW4, Y, stream=None):

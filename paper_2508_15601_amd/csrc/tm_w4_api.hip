@@ -1324,14 +1324,23 @@ int tm_gemm_w4a16_grouped_act(const uint16_t* X, const tm_expert_group* group, c
 
 int tm_get_grouped_plan(const tm_expert_group* group, int total_rows, int* variant, int* strips)
 {
+    return tm_get_grouped_form(group, total_rows, variant, strips, nullptr, nullptr);
+}
+
+int tm_get_grouped_form(const tm_expert_group* group, int total_rows, int* variant, int* strips, int* threads, int* pass_rows)
+{
     if (!valid(group)) return fail(TM_EINVAL, "expert group is null or invalid");
     if (total_rows <= 0) return fail(TM_EINVAL, "total_rows = %d out of range", total_rows);
     int dev = group->device;
     int cu = (dev >= 0 && dev < kMaxDevices && g_dev[dev].checked) ? g_dev[dev].num_cu : 256;
-    int v, st;
+    int v, st, pass_log, lds;
     grouped_plan(group, total_rows, cu, &v, &st);
+    Plan one{};
+    const bool one_shot = grouped_one_shot(group, total_rows, v, st, cu, &one, &pass_log, &lds);
     if (variant) *variant = v;
-    if (strips) *strips = st;
+    if (strips) *strips = one_shot ? one.strips : st;
+    if (threads) *threads = one_shot ? (int)one.block : 0;
+    if (pass_rows) *pass_rows = one_shot ? 1 << pass_log : 0;
     return TM_OK;
 }
 

@@ -64,6 +64,7 @@ int main()
     CHECK(tm_gemm_w4a16_grouped(fake16, nullptr, (const int32_t*)fake32, out16, 4, nullptr) == TM_EINVAL);
     CHECK(tm_gemm_w4a16_grouped_act(fake16, nullptr, (const int32_t*)fake32, out16, 4, 1, nullptr) == TM_EINVAL);
     CHECK(tm_get_grouped_plan(nullptr, 4, nullptr, nullptr) == TM_EINVAL);
+    CHECK(tm_get_grouped_form(nullptr, 4, nullptr, nullptr, nullptr, nullptr) == TM_EINVAL);
     tm_free_expert_group(nullptr);
     CHECK(tm_set_variant(99, 0) == TM_EINVAL && tm_set_variant(-2, 0) == TM_EINVAL && tm_set_variant(0, 1000) == TM_EINVAL);
     CHECK(tm_set_variant(-1, 0) == TM_OK);

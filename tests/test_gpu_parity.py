@@ -862,6 +862,24 @@ def test_grouped_gemm_small_ctas_against_oracle(tm, oracle, E, K, N, g, counts):
     test_grouped_gemm_against_oracle(tm, oracle, E, K, N, g, counts, 1, 2, -1)
 
 
+# the form each of them takes: (threads of a CTA, rows of an expert at a time)
+GROUPED_SMALL_FORMS = [(256, 16), (256, 16), (256, 8), (256, 8), (256, 8), (512, 8), (1024, 16), (512, 8)]
+
+
+@pytest.mark.parametrize("case,form", zip(GROUPED_SMALL_CASES, GROUPED_SMALL_FORMS))
+def test_grouped_gemm_form(tm, case, form):
+    """Groups of 64 at K above 2048 (the seventh) stay on the large CTAs, as does a load of many rows per expert."""
+    E, K, N, g, counts = case
+    _, dev = _make_experts(tm, np.random.default_rng(K), 1, K, N, g)
+    group = tm.tm_group_experts(dev * E)
+    rows = sum(counts)
+    variant, strips, threads, pass_rows = tm.tm_get_grouped_form(group, rows)
+    assert (threads, pass_rows) == form
+    assert tm.tm_get_grouped_plan(group, rows) == (variant, strips)
+    assert tm.tm_get_grouped_form(group, 64 * E)[2:] == (0, 0)
+    group.close()
+
+
 # the same launch over 8-bit integer and FP8 experts: decode-sized loads (every strip width the dispatcher picks), loads
 # taken in passes, prefill-sized loads on both CTA tiles
 GROUPED_8BIT_CASES = [
