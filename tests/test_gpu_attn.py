@@ -586,6 +586,52 @@ def test_attn_prefill_row_tiles(tm, B, Hkv, G, cap, positions, n, bits):
     cache.close()
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,Hkv,G,cap,n,rows", [(32, 16, 3, 128, 70, 256), (8, 16, 3, 128, 70, 128), (4, 16, 20, 96, 32, 256),
+                                                (16, 32, 1, 128, 120, 128), (1, 8, 4, 1344, 1000, 128), (2, 8, 8, 960, 600, 256),
+                                                (1, 1, 8, 2048, 40, 0)])
+def test_attn_prefill_rows_of_a_cta(tm, B, Hkv, G, cap, n, rows, bits):
+    """The cases of test_attn_prefill_row_tiles run on CTAs of as many rows as they are written for (0: the 16-column kernel)."""
+    cache = tm.tm_kv_create(B, Hkv, cap, bits)
+    assert tm.tm_get_attn_plan(cache, Hkv * G, count=n) == (1, rows)
+    cache.close()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("B,Hkv,G,past,n,rows", [(1, 8, 4, 331, 1000, 128), (2, 8, 8, 331, 600, 256), (1, 1, 8, 331, 40, 0)])
+def test_attn_prefill_moving_references(tm, B, Hkv, G, past, n, rows, bits):
+    """Scores that climb along the context by 2^58 in all, or fall, and that change by 2^35 from one run of 32 tokens to the next:
+    real rows have to move their softmax reference again and again, and the two wave groups of a 128-row CTA, which take the runs
+    in turn, meet with references that far apart."""
+    import torch
+    T = past + n
+    _say(f"attn prefill moving references B={B} Hkv={Hkv} G={G} n={n} bits={bits}")
+    rng = np.random.default_rng(n + bits)
+    u = rng.standard_normal(128)
+    u /= np.linalg.norm(u)
+    t = np.arange(T)
+    climb = 40.0 * t / T - 20.0 + np.where(t // 32 % 2, 12.0, -12.0)              # the score, natural logarithm
+    K = (0.5 * rng.standard_normal((B, Hkv, T, 128)) + (climb * 128 ** 0.5 / 8)[:, None] * u).astype(np.float16)
+    V = rng.standard_normal((B, Hkv, T, 128)).astype(np.float16)
+    sign = np.where(np.arange(Hkv * G) % 2, -1.0, 1.0)                            # every second head sees them fall
+    Q = (8 * sign[:, None] * u + 0.2 * rng.standard_normal((B, n, Hkv * G, 128))).astype(np.float16)
+    cache = tm.tm_kv_create(B, Hkv, T, bits)
+    assert tm.tm_get_attn_plan(cache, Hkv * G, count=n) == (1, rows)
+    zero, at = (torch.full((B,), x, dtype=torch.int32, device="cuda") for x in (0, past))
+    tm.tm_kv_append(cache, _dev(K.transpose(0, 2, 1, 3)), _dev(V.transpose(0, 2, 1, 3)), zero)
+    O = torch.full((B, n, Hkv * G, 128), float("nan"), dtype=torch.float16, device="cuda")
+    tm.tm_attn_prefill(_dev(Q), cache, at, O, 128 ** -0.5)
+    torch.cuda.synchronize()
+    O = O.cpu().numpy()
+    assert not np.isnan(O).any()
+    kq, vq = oa.kv_quantise(K, bits), oa.kv_quantise(V, bits)
+    for i in sorted({0, 1, n // 3, n // 2, n - 2, n - 1, *rng.integers(0, n, 6).tolist()}):
+        ref = oa.attn_prefill(Q[:, i:i + 1], *kq, *vq, np.full(B, past + i, np.int32), np.ones(B, np.int32), 128 ** -0.5)
+        ok, worst, fro = _close(O[:, i:i + 1], ref)
+        assert ok, (i, worst, fro)
+    cache.close()
+
+
 def test_attn_prefill_argument_checks(tm):
     import torch
     cache = tm.tm_kv_create(1, 2, 64, 8)
