@@ -1,4 +1,4 @@
-// Decode attention over an 8-bit KV cache (paper Sec. 3.3 attention pipeline; Sec. 4.2, 4.3, 4.4), and the kernel that
+// Decode attention over an 8-bit or 4-bit KV cache (paper Sec. 3.3 attention pipeline; Sec. 4.2, 4.3, 4.4), and the kernel that
 // quantises new keys / values into the cache.
 //
 // What differs from the paper's design, which rearranges Q in shared memory so that a 32-lane fragment load of the
@@ -19,7 +19,8 @@
 //     had every instruction touch half of sixteen 128-byte rows: 4.1 instead of 5.7 TB/s).
 //   - The codes of the next two 32-token blocks are in flight in registers while the current block is multiplied; the
 //     blocks' scale/zero words go through a small per-wave LDS ring (direct-to-LDS loads); a CTA's waves take blocks
-//     round-robin and meet in LDS at the end; long contexts are split across CTAs and merged by a second, tiny kernel.
+//     round-robin and meet in LDS at the end; long contexts are split across CTAs and merged by the CTA that arrives last, or,
+//     above sixteen pieces, by a second, tiny kernel.
 #include "tm_w4_host.h"
 
 namespace tmw4 {
@@ -32,8 +33,9 @@ constexpr float kNegBig = -1.0e30f;     // "minus infinity" that stays finite un
 constexpr float kMaskFloor = -1.0e20f;  // far below any score, far above kNegBig: exp2(kNegBig - kMaskFloor) is 0
 constexpr int kNonTemporal = 2;         // cache-policy bit of a buffer load: streamed once, do not keep
 
-// 2^x by the hardware instruction alone: arguments here are <= 0 and a result below the smallest normal number may
-// flush to zero (the library function spends four more instructions per call on that range).
+// 2^x by the hardware instruction alone: arguments here are at most kSlack (a score less a reference that may lag behind the largest
+// score by that much; the product with a value's scale still fits fp16, see SoftmaxState), and a result below the smallest
+// normal number may flush to zero (the library function spends four more instructions per call on that range).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 __device__ __forceinline__ float xor_max(float v, int mask) { return fmaxf(v, __shfl_xor(v, mask)); }
@@ -791,8 +793,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     const f32x4 neg_qbias = {-qbias, -qbias, -qbias, -qbias};
 
-    // (at prefill a wave may meet blocks in which some column has no live token yet: the running maximum then starts
-    // above the mask value, so that masked scores still turn into zero probabilities)
+    // The first block of a decoding step exceeds the reference kNegBig by more than kSlack in every column, which moves it to that
+    // block's largest score.  (At prefill a wave may meet blocks in which some column has no live token yet: the reference then
+    // starts above the mask value, so that masked scores still turn into zero probabilities.)
     SoftmaxState st{PREFILL ? kMaskFloor : kNegBig, 0.f, 0.f};
     f32x4 acc[8];
 #pragma unroll
