@@ -1041,17 +1041,17 @@ int attn_decode_splits(const AttnCache& kv, int max_len, int num_cu, int* blocks
     const int segs = kv.batch * kv.heads;
     int splits = segs >= num_cu ? 1 : num_cu / segs;
     // Two CTAs per CU (rounded up) over long contexts where one per CU leaves the most to a few of them (kv4/8 = bits of the codes,
-    // equal lengths / lengths between half and all, us):
+    // equal lengths / lengths between half and all, us; more in profiles/attn_decode_splits__sweep.txt):
     //   just over half the CUs                  1 split        3              4              5
-    //     136 pairs x 8192, kv4              34.7 / 32.9    31.7 / 30.6    35.6 / 27.1    32.0 / 29.4
-    //     144 pairs x 8192, kv8              54.5 / 47.5    51.3 / 47.7    56.9 / 43.6    52.6 / 49.6
-    //     144 pairs x 4096, kv8              29.0 / 26.9    28.6 / 27.2    32.7 / 27.6    29.8 / 27.4
-    //     160 pairs x 8192, kv8              54.9 / 47.7    55.5 / 51.0    60.2 / 54.3    63.8 / 50.9
+    //     136 pairs x 8192, kv4              35.6 / 33.1    31.7 / 30.9    35.9 / 26.7    31.9 / 28.3
+    //     144 pairs x 8192, kv8              55.3 / 47.6    52.2 / 47.7    58.0 / 43.4    53.0 / 48.8
+    //     144 pairs x 4096, kv8              29.9 / 27.5    28.9 / 28.1    32.6 / 26.5    29.9 / 26.6
+    //     160 pairs x 8192, kv8              55.4 / 48.1    56.4 / 51.8    60.5 / 53.7    64.0 / 50.0
     //   a few pairs more than CUs               1 split        2
-    //     272 pairs x 8192, kv4              70.4 / 51.8    62.9 / 45.5
-    //     320 pairs x 8192, kv8             119.4 / 100     112.7 / 92.9
-    //     352 pairs x 8192, kv4              71.7 / 61.2    68.2 / 62.5
-    //     272 pairs x 2048, kv8              32.3 / 27.9    31.3 / 25.5   (304 pairs: 32.9 / 28.4, 32.5 / 30.5)
+    //     272 pairs x 8192, kv4              71.9 / 52.5    63.7 / 45.7
+    //     320 pairs x 8192, kv8             120.8 / 99.8    114.9 / 93.7
+    //     352 pairs x 8192, kv4              73.7 / 62.4    70.7 / 62.1
+    //     288 pairs x 2048, kv8              32.9 / 25.9    31.9 / 24.6
     const bool half = segs * 2 > num_cu && segs * 16 <= num_cu * 9 && max_len >= 8192;
     const bool few_over = segs > num_cu && segs * 4 <= num_cu * 5 && nblk >= 128;
     if (half || few_over) splits = (2 * num_cu + segs - 1) / segs;

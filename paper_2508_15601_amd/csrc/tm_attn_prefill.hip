@@ -21,10 +21,11 @@
 // With fewer rows two groups of four waves (RW = 4, 128 rows) split the context instead: each takes every second run of 32
 // tokens, and they meet in LDS at the end.
 //
-// Measured (32 query / 8 KV heads, 4000 tokens, 8-bit / 4-bit codes; the 16-column kernel ran this before): 345 -> 149-158 us /
+// Measured (32 query / 8 KV heads, 4000 tokens, 8-bit / 4-bit codes; the 16-column kernel ran this before): 345 -> 152-162 us /
 // 289 -> 150 us; 64 / 8 heads, 2048 tokens after 6000, 4-bit: 880 -> 465 us = 1.0 PFLOP/s, half of what an MFMA-only loop sustains
-// on this chip.  What bounds it is vector and matrix issue together: a 32-token run is 16 MFMAs of 32 clocks and about 100
-// vector instructions of 4, two waves per SIMD, 55 % of the clocks in the matrix pipe.  Forced interleaving of the two
+// on this chip.  What bounds it is vector and matrix issue together, and the uneven end of a causal launch: a 32-token run is 16
+// MFMAs of 32 clocks and 140-150 vector instructions (conversion included), two waves per SIMD; over the whole launch of 4000 tokens
+// the matrix pipe is busy 35-37 % of the clocks, the vector pipes issue in 27 % of the waves' time.  Forced interleaving of the two
 // (scheduling groups of one MFMA, seven vector instructions, one LDS read) is 6-9 % slower than the compiler's own order, wave
 // priorities change nothing.
 #include "tm_w4_host.h"
@@ -400,8 +401,9 @@ hipError_t attn_prefill_setup()
 // capacity.  Where that is little more than the chunk, the CTAs of a launch attend over anything between nothing and all of it:
 // further rounds fill up evenly, but a launch of one round lasts as long as its longest CTA, up to twice the average (less in
 // short chunks, where fixed costs count).  Where the capacity is much larger the CTAs are taken to be alike and rounds to be whole.
-// With 2.4 and 3.85 no launch of 240 random ones (16 ... 8192 tokens, 0 ... 16384 before them, 1 ... 32 KV heads, batch 1 ... 8) ran
-// slower than in the 16-column form; they average 1.28 times its speed, within 1 % of the best form of each.
+// With 2.4 and 3.85 none of 110 random launches (16 ... 8192 tokens, 0 ... 16384 before them, 1 ... 32 KV heads, batch 1 ... 8, capacity
+// one, two or eight times the context) that leave the 16-column form is slower for it; all of them average 1.33 times its speed, 0.3 %
+// behind the fastest form of each, the worst 23 % (profiles/attn_prefill_rule__random_launches.txt).
 int attn_prefill_rows(const AttnCache& kv, int count, int q_heads, int num_cu)
 {
     const long bh = (long)kv.batch * kv.heads;

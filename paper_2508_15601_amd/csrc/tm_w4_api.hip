@@ -219,11 +219,13 @@ static bool deep_narrow_tile64(const tm_packed_w4* h, int M, int num_cu)
 // The CTA tile of an 8-bit launch of more than 64 rows: the largest one that gives every CU a CTA, unless another is estimated
 // to be faster by 8 % or more.  What the first rule does not see is the last round: K = 4096, N = 12288, M = 700 (FP8) makes 288
 // tiles of 128 x 256, 32 of which run while the other CUs wait (97.8 us; 81.9 us on 1056 tiles of 64 x 128).  The estimate is a
-// least-squares fit to the unsplit ones of 12000 timed plans of 1968 random layers (K 1024 ... 28672, N 1024 ... 32768, M 65 ... 4096,
-// int8 and FP8, every group; rms error 5-9 %): a fixed part, the K loop (apart for launches of one round, whose CTAs have more wave sets,
+// least-squares fit to timed unsplit plans of random layers (K 1024 ... 28672, N 1024 ... 32768, M 65 ... 4096,
+// int8 and FP8, every group): a fixed part, the K loop (apart for launches of one round, whose CTAs have more wave sets,
 // and of several; per round, and by the load on average), more of it where groups of 32 double the scales, and the output's store.
-// On 3690 other random layers it changes every fourth choice: those run 1.20 times as fast on average, one of them 5 % slower.  Launches that the first rule leaves so small that K may be split keep that rule's tile, and no other tile is taken
-// that may split: a call needs the scratch it always did.
+// On 84 other random layers (profiles/tile_rule_8bit__random_layers.txt) it changes every fourth choice: those run 1.16 times as fast
+// on average, one of them 1 % slower; all of them are 0.4 % behind the fastest forced tile on average.  Launches that the first rule
+// leaves so small that K may be split keep that rule's tile, and no other tile is taken that may split: a call needs the scratch it
+// always did.
 static int choose_tile_8bit(int M, int K, int N, int group, int num_cu)
 {
     struct Shape {
