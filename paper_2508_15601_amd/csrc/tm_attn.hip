@@ -12,8 +12,8 @@
 //     leaves its registers either; the cache stores V in blocks of 32 tokens in that operand order.
 //   - Scale and zero-point are per token, i.e. per row of S^T and per k-index of the second product: they are applied
 //     to four scores and eight probabilities per lane and block instead of to 2 x 128 code values per token.  The codes
-//     enter the matrix cores as 1024 + q (one byte permute per two codes; values of 8-bit codes as q); the bias of the keys
-//     and the zero-points leave through fp32 terms per query head, the bias of 4-bit values once per run of tokens.
+//     enter the matrix cores as 1024 + q (one byte permute per two codes); the bias of the keys and the zero-points leave
+//     through fp32 terms per query head, the bias of the values block by block.
 //   - The cache itself is stored in operand order (blocks of 32 tokens x 128 dimensions), the hardware-aware packing of
 //     the weights applied to K and V: every load instruction of a wave reads 1 KiB of consecutive bytes (row-major keys
 //     had every instruction touch half of sixteen 128-byte rows: 4.1 instead of 5.7 TB/s).
@@ -469,6 +469,7 @@ __device__ __forceinline__ void load_block(BlockRegs& r, uint32_t* sz_slot, cons
 // dependent instructions that two waves per SIMD cannot hide.  Probabilities of at most 2^kSlack times a scale fit fp16.
 struct SoftmaxState {
     float m_run, l_run, corr;
+    f32x4 bias;                            // 8-bit codes: minus the value bias that acc carries at the moment
 };
 template <int BITS>
 constexpr float kSlack = BITS == 8 ? 6.0f : 2.0f;      // 2^6 * (2 * 65504 / 255), 2^2 * (2 * 65504 / 15) < 65504
@@ -479,7 +480,7 @@ __device__ __forceinline__ uint32_t swap_half_rows(uint32_t v)
 }
 
 // Moves the reference to the largest score of every query head so far (mx: the lane's largest new score, not reduced).
-template <bool PACK>
+template <int BITS, bool PACK>
 __device__ __forceinline__ void move_reference(float mx, SoftmaxState& st, f32x4 (&acc)[8])
 {
     if constexpr (PACK) mx = fmaxf(mx, __builtin_bit_cast(float, swap_half_rows(__builtin_bit_cast(uint32_t, mx))));
@@ -489,6 +490,7 @@ __device__ __forceinline__ void move_reference(float mx, SoftmaxState& st, f32x4
     st.m_run = m_new;
     st.l_run *= alpha;
     st.corr *= alpha;
+    if constexpr (BITS == 8) st.bias *= alpha;
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= alpha;
 }
@@ -571,7 +573,7 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
     scores(st.m_run);
     if (__any(mx > kSlack<BITS>)) {
         scores(0.0f);
-        move_reference<PACK>(mx, st, acc);
+        move_reference<BITS, PACK>(mx, st, acc);
         scores(st.m_run);
     }
     // probability times the value scale of that token, rounded to fp16: the operand of the second product.  The zero-point
@@ -596,7 +598,7 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
             own[j][0] = (uint32_t)__builtin_bit_cast(uint16_t, q[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[1]) << 16);
             own[j][1] = (uint32_t)__builtin_bit_cast(uint16_t, q[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, q[3]) << 16);
             asm volatile("" : "+v"(own[j][0]), "+v"(own[j][1]));
-            // sum over the lane's tokens of z * p'; the bias leaves below
+            // sum over the lane's tokens of z * p'
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 const f16x2 two = as_f16x2(own[j][rr >> 1]);
@@ -619,17 +621,21 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
     st.l_run += psum;
     st.corr += zsum;
     // The bias of a value code is several times the payload (4-bit codes: up to a hundred times): carried along to the end of
-    // a long context it would cost the sums their low bits, in proportion to the context.  8-bit codes lose it before the product
-    // (1024 + q - 1024 is exact).  For 4-bit codes, which bring half the bytes per instruction, one product with the constant operand -bias
-    // (1024, or 64 at the k-values 2, 3, 6 and 7 of a word) takes it out run by run, before the codes that carry it go in.
+    // a long context it would cost the sums their low bits, in proportion to the context.  Products with the constant operand -bias
+    // (1024; 64 at the k-values 2, 3, 6 and 7 of a 4-bit word) sum up what has to leave.  4-bit codes: per block, before the codes
+    // that carry it go in.  8-bit codes: every fourth block (128 tokens times 1151 are a seventh of the 8192 times 127 that the codes
+    // themselves sum up to over 32768 tokens; taken out of every code before the product it cost the 16-column prompt form up to 8 %:
+    // 64 tokens after 12000, 8 heads: 65.2 us, like this 60.9).
+    const _Float16 bias_a = (_Float16)-1024.0f, bias_b = BITS == 8 ? bias_a : (_Float16)-64.0f;
+    const f16x8 minus_bias = {bias_a, bias_a, bias_b, bias_b, bias_a, bias_a, bias_b, bias_b};
     if constexpr (BITS == 4) {
-        const _Float16 a = (_Float16)-1024.0f, b = (_Float16)-64.0f;
-        const f16x8 minus_bias = {a, a, b, b, a, a, b, b};
         f32x4 bias = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int n = 0; n < NH; ++n) bias = mfma16x16x32(minus_bias, pb[n], bias);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += bias;
+    } else {
+        st.bias = mfma16x16x32(minus_bias, pb[0], st.bias);
     }
     // O^T += V^T P'^T : rows = dimensions (eight 16-row tiles), k = the 32 tokens of a run
 #pragma unroll
@@ -639,12 +645,19 @@ __device__ __forceinline__ void process_runs(const BlockRegs& r, const uint32_t*
             f16x8 a;
             if constexpr (BITS == 8) {
                 const u32x4 w = r.v[i >> 1];
-                a = ((i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y)) - (_Float16)1024.0f;
+                a = (i & 1) ? biased8_w8(w.z, w.w) : biased8_w8(w.x, w.y);
             } else {
                 a = biased8(r.v[2 * (N0 + n) + (i >> 2)][i & 3], mg);
             }
             acc[i] = mfma16x16x32(a, pb[n], acc[i]);
         }
+    if constexpr (BITS == 8) {
+        if ((blk >> 2 & 3) == 3) {                           // (wave-uniform) a wave takes every fourth block
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += st.bias;
+            st.bias = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
 }
 
 // A whole block.  The two runs of a 4-bit block go through together, which gives each wave two independent chains of
@@ -796,7 +809,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // The first block of a decoding step exceeds the reference kNegBig by more than kSlack in every column, which moves it to that
     // block's largest score.  (At prefill a wave may meet blocks in which some column has no live token yet: the reference then
     // starts above the mask value, so that masked scores still turn into zero probabilities.)
-    SoftmaxState st{PREFILL ? kMaskFloor : kNegBig, 0.f, 0.f};
+    SoftmaxState st{PREFILL ? kMaskFloor : kNegBig, 0.f, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
     f32x4 acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -832,7 +845,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) sm_out[wave][i][rr][lane] = acc[i][rr] - corr_w;   // the zero-points leave here
+        for (int rr = 0; rr < 4; ++rr)                       // the zero-points leave here
+            sm_out[wave][i][rr][lane] = (BITS == 8 ? acc[i][rr] + st.bias[rr] : acc[i][rr]) - corr_w;
     __syncthreads();
     // thread (wave w, lane) finalises row tiles 2w and 2w+1 of its column
     float M = kNegBig;

@@ -289,6 +289,7 @@ def test_attn_decode_sums_of_a_long_context(tm, bits, G):
     a value's scale: a wave adds up 8192 codes of 127 on average, so its sums end near 2^20, where an fp32 ulp is 1/16 (0.036 rms on the
     way there).  256 products with, at four values a step, eight roundings of 0.29 ulp each make 0.47, the four waves 0.94; the
     result before the division is 42 * sqrt(32768) = 7600: 1.2e-4 of it (4-bit codes: sums and result are both 17 times smaller).
+    (The bias of 1024 per code stays for 128 tokens at most, a seventh of those sums.)
     Twice that is allowed.  Sums that carry a conversion bias of 1024 per token to the end are eight times as long: 1e-3."""
     import torch
     B, Hkv, T = 64, 4, 32768
