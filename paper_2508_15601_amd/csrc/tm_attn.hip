@@ -1057,15 +1057,15 @@ int attn_decode_splits(const AttnCache& kv, int max_len, int num_cu, int* blocks
     // Two CTAs per CU (rounded up) over long contexts where one per CU leaves the most to a few of them (kv4/8 = bits of the codes,
     // equal lengths / lengths between half and all, us; more in profiles/attn_decode_splits__sweep.txt):
     //   just over half the CUs                  1 split        3              4              5
-    //     136 pairs x 8192, kv4              35.6 / 33.1    31.7 / 30.9    35.9 / 26.7    31.9 / 28.3
-    //     144 pairs x 8192, kv8              55.3 / 47.6    52.2 / 47.7    58.0 / 43.4    53.0 / 48.8
-    //     144 pairs x 4096, kv8              29.9 / 27.5    28.9 / 28.1    32.6 / 26.5    29.9 / 26.6
-    //     160 pairs x 8192, kv8              55.4 / 48.1    56.4 / 51.8    60.5 / 53.7    64.0 / 50.0
+    //     136 pairs x 8192, kv4              35.2 / 33.2      31.8 / 30.8      36.1 / 26.8      31.8 / 28.5
+    //     144 pairs x 8192, kv8              54.3 / 48.2      51.9 / 48.8      57.7 / 43.7      53.4 / 50.7
+    //     144 pairs x 4096, kv8              29.5 / 27.9      28.6 / 26.7      32.7 / 27.0      29.0 / 29.6
+    //     160 pairs x 8192, kv8              55.6 / 48.7      56.8 / 52.8      61.3 / 54.4      64.0 / 51.9
     //   a few pairs more than CUs               1 split        2
-    //     272 pairs x 8192, kv4              71.9 / 52.5    63.7 / 45.7
-    //     320 pairs x 8192, kv8             120.8 / 99.8    114.9 / 93.7
-    //     352 pairs x 8192, kv4              73.7 / 62.4    70.7 / 62.1
-    //     288 pairs x 2048, kv8              32.9 / 25.9    31.9 / 24.6
+    //     272 pairs x 8192, kv4              70.8 / 51.8      63.1 / 45.6
+    //     320 pairs x 8192, kv8             120.7 / 100.5    113.8 / 92.0
+    //     352 pairs x 8192, kv4              72.3 / 62.7      69.0 / 62.7
+    //     288 pairs x 2048, kv8              32.6 / 25.3      32.6 / 25.1
     const bool half = segs * 2 > num_cu && segs * 16 <= num_cu * 9 && max_len >= 8192;
     const bool few_over = segs > num_cu && segs * 4 <= num_cu * 5 && nblk >= 128;
     if (half || few_over) splits = (2 * num_cu + segs - 1) / segs;

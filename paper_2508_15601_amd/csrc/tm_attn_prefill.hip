@@ -402,8 +402,8 @@ hipError_t attn_prefill_setup()
 // further rounds fill up evenly, but a launch of one round lasts as long as its longest CTA, up to twice the average (less in
 // short chunks, where fixed costs count).  Where the capacity is much larger the CTAs are taken to be alike and rounds to be whole.
 // With 2.4 and 3.85 none of 110 random launches (16 ... 8192 tokens, 0 ... 16384 before them, 1 ... 32 KV heads, batch 1 ... 8, capacity
-// one, two or eight times the context) that leave the 16-column form is slower for it; all of them average 1.33 times its speed, 0.3 %
-// behind the fastest form of each, the worst 23 % (profiles/attn_prefill_rule__random_launches.txt).
+// one, two or eight times the context) that leave the 16-column form is slower for it; all of them average 1.32 times its speed and that
+// of the fastest form of each, the worst is 26 % behind it (profiles/attn_prefill_rule__random_launches.txt).
 int attn_prefill_rows(const AttnCache& kv, int count, int q_heads, int num_cu)
 {
     const long bh = (long)kv.batch * kv.heads;
