@@ -42,8 +42,8 @@ __device__ __forceinline__ float xor_max(float v, int mask) { return fmaxf(v, __
 __device__ __forceinline__ float xor_add(float v, int mask) { return v + __shfl_xor(v, mask); }
 
 // ------------------------------------------------------------------------------------------------ quantise + store
-// Minimum and maximum over the wave, in every lane: rotations within the rows of sixteen lanes, then swaps between rows.
-__device__ __forceinline__ void wave_min_max(float& mn, float& mx)
+// Minimum and maximum over every row of sixteen lanes, in each of its lanes.
+__device__ __forceinline__ void row_min_max(float& mn, float& mx)
 {
     auto fold = [&](auto CTRL) {
         constexpr int ctrl = decltype(CTRL)::value;        // row_ror by 8, 4, 2, 1
@@ -56,6 +56,12 @@ __device__ __forceinline__ void wave_min_max(float& mn, float& mx)
     fold(std::integral_constant<int, 0x124>{});
     fold(std::integral_constant<int, 0x122>{});
     fold(std::integral_constant<int, 0x121>{});
+}
+
+// The same over the wave: rows first, then swaps between rows.
+__device__ __forceinline__ void wave_min_max(float& mn, float& mx)
+{
+    row_min_max(mn, mx);
 #if defined(__HIP_DEVICE_COMPILE__)
     auto pair = [](auto r, auto f) { return f(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])); };
     auto lo = [](float x, float y) { return fminf(x, y); };
@@ -69,23 +75,105 @@ __device__ __forceinline__ void wave_min_max(float& mn, float& mx)
 #endif
 }
 
+// a / b rounded to nearest, exactly as the division gives it, from the correctly rounded reciprocal of b: a product and one
+// correction, three instructions where a division is ten.  Checked against the division for every finite fp16 a over every
+// finite positive fp16 b, and for every difference of two finite fp16 numbers over 15 and 255.
+__device__ __forceinline__ float quotient(float a, float b, float inv)
+{
+    const float q = a * inv;
+    return __builtin_fmaf(__builtin_fmaf(-q, b, a), inv, q);
+}
+
+// Scale and zero-point of a vector from its extremes, and the codes of its values: scale = range / levels rounded to fp16 (1 where
+// that is zero or not finite), code = round(x / scale) + zero-point, within the levels.
+template <int BITS>
+struct Quantiser {
+    static constexpr float top = BITS == 8 ? 255.0f : 15.0f;
+    _Float16 s16;
+    float s, inv, zero;
+    bool odd;                              // the scale was replaced by 1 (only then can a value be infinite)
+
+    __device__ __forceinline__ Quantiser(float mn, float mx)
+    {
+        s16 = (_Float16)quotient(mx - mn, top, 1.0f / top);
+        s = (float)s16;
+        odd = !(s > 0.0f) || __builtin_isinf(s);
+        if (odd) {
+            s = 1.0f;
+            s16 = (_Float16)1.0f;
+        }
+        const float r = __builtin_amdgcn_rcpf(s);            // within an ulp; one step makes it the nearest number
+        inv = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+        zero = fminf(fmaxf(rintf(over_scale(-mn)), 0.0f), top);
+    }
+    __device__ __forceinline__ float over_scale(float x) const { return odd ? x : quotient(x, s, inv); }
+    __device__ __forceinline__ uint32_t code(float x) const { return (uint32_t)fminf(fmaxf(rintf(over_scale(x)) + zero, 0.0f), top); }
+    __device__ __forceinline__ uint32_t pair() const
+    {
+        return (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, (_Float16)zero) << 16);
+    }
+};
+
 // The codes of the lane's two values and the vector's scale / zero word.
 template <int BITS>
 __device__ __forceinline__ uint32_t quantise_pair(float x0, float x1, uint32_t& q0, uint32_t& q1)
 {
-    constexpr float top = BITS == 8 ? 255.0f : 15.0f;
     float mn = fminf(x0, x1), mx = fmaxf(x0, x1);
     wave_min_max(mn, mx);
-    _Float16 s16 = (_Float16)((mx - mn) / top);
-    float sf = (float)s16;
-    if (!(sf > 0.0f) || __builtin_isinf(sf)) {
-        sf = 1.0f;
-        s16 = (_Float16)1.0f;
+    const Quantiser<BITS> z(mn, mx);
+    q0 = z.code(x0);
+    q1 = z.code(x1);
+    return z.pair();
+}
+
+// The block-wise appends: sixteen lanes hold a vector, eight dimensions each.  A thread's four vectors (two tokens, keys then
+// values; `it` of vector it) are all requested before the first is used: one round trip to memory instead of four in a row.
+// What bounds these kernels is the arithmetic of the codes beside that round trip; with four requests in a row and a division per
+// value, 4000 tokens x 8 heads took 10.8 us (8-bit) and 10.2 (4-bit), now 8.0 and 7.2; 100 tokens 5.1, now 3.7.
+struct AppendSlot {
+    int u;                                 // token of the 32-token block
+    bool live;
+};
+__device__ __forceinline__ AppendSlot append_slot(int it, int u0, int u1)
+{
+    const int u = (int)(threadIdx.x >> 6) * 8 + (it & 1) * 4 + (int)((threadIdx.x & 63) >> 4);
+    return AppendSlot{u, u >= u0 && u < u1};
+}
+__device__ __forceinline__ void append_request(u32x4 (&raw)[4], const uint16_t* Kn, const uint16_t* Vn, int heads, int h, int b,
+                                               int count, long first_token, int u0, int u1)
+{
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const AppendSlot a = append_slot(it, u0, u1);
+        raw[it] = u32x4{0u, 0u, 0u, 0u};
+        if (a.live) {
+            const size_t src = (((size_t)b * count + (size_t)(first_token + a.u)) * heads + h) * kHeadDim + 8 * (threadIdx.x & 15);
+            raw[it] = *reinterpret_cast<const u32x4*>((it >> 1 ? Vn : Kn) + src);
+        }
     }
-    const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), top);
-    q0 = (uint32_t)fminf(fmaxf(rintf(x0 / sf) + zf, 0.0f), top);
-    q1 = (uint32_t)fminf(fmaxf(rintf(x1 / sf) + zf, 0.0f), top);
-    return (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, (_Float16)zf) << 16);
+}
+// The codes of the lane's eight values and the vector's scale / zero word.
+template <int BITS>
+__device__ __forceinline__ uint32_t quantise_row8(const u32x4& raw, uint32_t (&q)[8])
+{
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const f16x2 two = as_f16x2(raw[k]);
+        x[2 * k] = (float)two.x;
+        x[2 * k + 1] = (float)two.y;
+    }
+    float mn = x[0], mx = x[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) {
+        mn = fminf(mn, x[k]);
+        mx = fmaxf(mx, x[k]);
+    }
+    row_min_max(mn, mx);
+    const Quantiser<BITS> z(mn, mx);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) q[k] = z.code(x[k]);
+    return z.pair();
 }
 
 // The append of a decoding step (few tokens).  A CTA of two waves per (sequence, new token, KV head): one quantises the
@@ -150,49 +238,17 @@ __global__ __launch_bounds__(256) void kv_append_block_kernel(AttnCache kv, cons
     const long t1 = last < (long)(tb + 1) * 32 ? last : (long)(tb + 1) * 32;
     if (t0 >= t1) return;                                              // CTA-uniform
     const int u0 = (int)(t0 - (long)tb * 32), u1 = (int)(t1 - (long)tb * 32);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sub = lane & 15;                                         // dimensions 8*sub .. 8*sub + 7
+    const int sub = threadIdx.x & 15;                                  // dimensions 8*sub .. 8*sub + 7
     const size_t bh = (size_t)b * kv.heads + h;
+    u32x4 raw[4];
+    append_request(raw, Kn, Vn, kv.heads, h, b, count, (long)tb * 32 - pos, u0, u1);
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int which = it >> 1;                                     // 0: keys, 1: values
-        const int u = wave * 8 + (it & 1) * 4 + (lane >> 4);           // token of the block
-        const bool live = u >= u0 && u < u1;
-        const long t = (long)tb * 32 + u;
-        float x[8];
-        if (live) {
-            const size_t src = (((size_t)b * count + (size_t)(t - pos)) * kv.heads + h) * kHeadDim + 8 * sub;
-            const u32x4 raw = *reinterpret_cast<const u32x4*>((which ? Vn : Kn) + src);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                x[2 * k] = (float)__builtin_bit_cast(_Float16, (unsigned short)(raw[k] & 0xffffu));
-                x[2 * k + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(raw[k] >> 16));
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = 0.f;
-        }
-        float mn = x[0], mx = x[0];
-#pragma unroll
-        for (int k = 1; k < 8; ++k) {
-            mn = fminf(mn, x[k]);
-            mx = fmaxf(mx, x[k]);
-        }
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {
-            mn = fminf(mn, __shfl_xor(mn, m));
-            mx = fmaxf(mx, __shfl_xor(mx, m));
-        }
-        _Float16 s16 = (_Float16)((mx - mn) / 255.0f);
-        float sf = (float)s16;
-        if (!(sf > 0.0f) || __builtin_isinf(sf)) {
-            sf = 1.0f;
-            s16 = (_Float16)1.0f;
-        }
-        const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), 255.0f);
+        const AppendSlot a = append_slot(it, u0, u1);
+        const int u = a.u;                                             // token of the block
         uint32_t q[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) q[k] = (uint32_t)fminf(fmaxf(rintf(x[k] / sf) + zf, 0.0f), 255.0f);
+        const uint32_t pair = quantise_row8<8>(raw[it], q);
         if (which == 0) {
             // dimensions 8*sub .. +7 of token u: eight consecutive bytes of chunk (j*2 + half)*64 + 16*hh + c
             const int d = 8 * sub;
@@ -209,11 +265,7 @@ __global__ __launch_bounds__(256) void kv_append_block_kernel(AttnCache kv, cons
                 lds[1][((i >> 1) * 64 + 16 * hh + (d & 15)) * 16 + (i & 1) * 8 + e] = (uint8_t)q[k];
             }
         }
-        if (live && sub == 0) {
-            const _Float16 z16 = (_Float16)zf;
-            kv.sz[(bh * kv.cap + t) * 2 + which] =
-                (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, z16) << 16);
-        }
+        if (a.live && sub == 0) kv.sz[(bh * kv.cap + (size_t)tb * 32 + u) * 2 + which] = pair;
     }
     __syncthreads();
     const size_t blk = (bh * (kv.cap / 32) + tb) * 4096;
@@ -267,49 +319,17 @@ __global__ __launch_bounds__(256) void kv4_append_block_kernel(AttnCache kv, con
     const long t1 = last < (long)(tb + 1) * 32 ? last : (long)(tb + 1) * 32;
     if (t0 >= t1) return;                                              // CTA-uniform
     const int u0 = (int)(t0 - (long)tb * 32), u1 = (int)(t1 - (long)tb * 32);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sub = lane & 15;                                         // dimensions 8*sub .. 8*sub + 7
+    const int sub = threadIdx.x & 15;                                  // dimensions 8*sub .. 8*sub + 7
     const size_t bh = (size_t)b * kv.heads + h;
+    u32x4 raw[4];
+    append_request(raw, Kn, Vn, kv.heads, h, b, count, (long)tb * 32 - pos, u0, u1);
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int which = it >> 1;
-        const int u = wave * 8 + (it & 1) * 4 + (lane >> 4);
-        const bool live = u >= u0 && u < u1;
-        const long t = (long)tb * 32 + u;
-        float x[8];
-        if (live) {
-            const size_t src = (((size_t)b * count + (size_t)(t - pos)) * kv.heads + h) * kHeadDim + 8 * sub;
-            const u32x4 raw = *reinterpret_cast<const u32x4*>((which ? Vn : Kn) + src);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                x[2 * k] = (float)__builtin_bit_cast(_Float16, (unsigned short)(raw[k] & 0xffffu));
-                x[2 * k + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(raw[k] >> 16));
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = 0.f;
-        }
-        float mn = x[0], mx = x[0];
-#pragma unroll
-        for (int k = 1; k < 8; ++k) {
-            mn = fminf(mn, x[k]);
-            mx = fmaxf(mx, x[k]);
-        }
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {
-            mn = fminf(mn, __shfl_xor(mn, m));
-            mx = fmaxf(mx, __shfl_xor(mx, m));
-        }
-        _Float16 s16 = (_Float16)((mx - mn) / 15.0f);
-        float sf = (float)s16;
-        if (!(sf > 0.0f) || __builtin_isinf(sf)) {
-            sf = 1.0f;
-            s16 = (_Float16)1.0f;
-        }
-        const float zf = fminf(fmaxf(rintf(-mn / sf), 0.0f), 15.0f);
+        const AppendSlot a = append_slot(it, u0, u1);
+        const int u = a.u;
         uint32_t q[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) q[k] = (uint32_t)fminf(fmaxf(rintf(x[k] / sf) + zf, 0.0f), 15.0f);
+        const uint32_t pair = quantise_row8<4>(raw[it], q);
         if (which == 0) {
             // dimensions 32*hh + 8*tt + e, e = 0..7: word tt of chunk (u/16)*64 + 16*hh + u%16; element e at nibble
             // e/2 + 4*(e % 2)
@@ -324,11 +344,7 @@ __global__ __launch_bounds__(256) void kv4_append_block_kernel(AttnCache kv, con
             w[1] = q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24);
             *reinterpret_cast<u32x2*>(&vcodes[u][8 * sub]) = w;
         }
-        if (live && sub == 0) {
-            const _Float16 z16 = (_Float16)zf;
-            kv.sz[(bh * kv.cap + t) * 2 + which] =
-                (uint32_t)__builtin_bit_cast(unsigned short, s16) | ((uint32_t)__builtin_bit_cast(unsigned short, z16) << 16);
-        }
+        if (a.live && sub == 0) kv.sz[(bh * kv.cap + (size_t)tb * 32 + u) * 2 + which] = pair;
     }
     __syncthreads();
     const size_t blk = (bh * (kv.cap / 32) + tb) * 2048;

@@ -76,6 +76,33 @@ def test_kv_append_bit_exact(tm, B, Hkv, T, chunks, bits):
 
 
 @pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("n", [1, 40])                       # the kernels of a decoding step and of a prompt
+def test_kv_append_extreme_values(tm, n, bits):
+    """Codes are those of the division, bit for bit, over the whole range of fp16: values of every exponent, vectors of subnormal
+    numbers only (a scale that rounds to a subnormal one, or to zero), infinities, a constant, the largest range."""
+    import torch
+    B, Hkv = 8, 3
+    _say(f"kv append extreme values n={n} bits={bits}")
+    rng = np.random.default_rng(n + bits)
+    x = rng.integers(0, 1 << 16, (2, B, n, Hkv, 128), np.uint16).view(np.float16)
+    x = np.where(np.isfinite(x), x, np.float16(0))           # every finite bit pattern
+    x[:, 1] = (x[:, 1].view(np.uint16) & 0x83ff).view(np.float16)            # subnormal
+    x[:, 2] = (x[:, 2].view(np.uint16) & 0x8007).view(np.float16)            # a range below half the smallest scale
+    x[:, 3, ..., 5] = np.inf
+    x[:, 4, ..., 9] = -np.inf
+    x[:, 5] = np.float16(0.37)
+    x[:, 6, ..., 0], x[:, 6, ..., 1] = np.float16(65504), np.float16(-65504)
+    cache = tm.tm_kv_create(B, Hkv, 64, bits)
+    tm.tm_kv_append(cache, _dev(x[0]), _dev(x[1]), torch.zeros(B, dtype=torch.int32, device="cuda"))
+    got = oa.kv_cache_unpack(*tm.tm_kv_download(cache), B, Hkv, cache.capacity, bits)
+    with np.errstate(all="ignore"):
+        want = [w for v in x for w in oa.kv_quantise(v.transpose(0, 2, 1, 3), bits)]
+    for g, w in zip(got, want):
+        assert np.array_equal(g[:, :, :n].astype(np.float32), w.astype(np.float32))
+    cache.close()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
 def test_kv_append_ragged_positions(tm, bits):
     """Sequences at different positions, runs that start and end inside a 32-token block (the block-wise kernel merges with
     what the cache holds), a run cut off by the capacity, and a run that starts before position 0."""
