@@ -158,6 +158,56 @@ bool valid(const tm_packed_w4* p) { return p && p->magic == kMagic; }
 bool valid(const tm_expert_group* g) { return g && g->magic == kGroupMagic; }
 int ceil_div(int a, int b);
 
+// The CTA tile of a grouped launch, 64 x 128 or 128 x 256, from an estimate of both.  The rows per expert live on the device; a
+// balanced routing spreads them like counts of that mean, of which seven values stand for all experts.  A row tile that an
+// expert does not fill runs as one of 32, 64 or 96 rows.  The estimate is a least-squares fit to timed launches (4-bit: 3594, 8-bit
+// formats: 5421; 4 ... 128 experts, K and N 1024 ... 14336 x 28672, mean 6 ... 700 rows, every group): a fixed part and, per 128
+// rows of K, of launches of at most one CTA per CU a part per CTA, per 16 rows of the longest CTA and per 16 rows and CU, of larger ones a
+// part per CTA and CU, per 16 rows and CU, and per round.  Its choices are 1.1 % (64 ... 800 rows) to 4 % (below) behind the faster
+// of the two on average, where 64 x 128 throughout is 9-16 % behind above 64 rows and 128 x 256 throughout 6-30 %: 8 experts of
+// 4096 x 28672 and 14336 x 4096, 250 rows: 565 + 343 us on 128 x 256 tiles, 547 + 281 on 64 x 128; 1000 rows of 4096 x 7168: 437 and 480.
+int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
+{
+    struct Shape {
+        int variant;
+        double one[4], more[4];         // us: fixed; then per 128 rows of K, in the order above
+        double one32, more32;           // groups of 32: more per 128 rows of K
+    };
+    static const Shape shapes[2][2] = {
+        {{kTile64x128, {3.76, 0.289, 0.065, 0.033}, {4.56, 0.149, 0.073, 0.194}, 0.114, 0.049},
+         {kTile128x256, {5.03, 0.665, 0.109, 0.073}, {7.05, 0.0, 0.183, 0.597}, 0.108, 0.081}},
+        {{kTile64x128, {3.63, 0.292, 0.042, 0.072}, {3.18, 0.487, 0.0, 0.216}, 0.061, 0.069},
+         {kTile128x256, {4.07, 0.566, 0.099, 0.128}, {2.40, 0.834, 0.097, 0.481}, 0.129, 0.229}}};
+    static const double spread[7] = {-1.5, -0.8, -0.4, 0.0, 0.4, 0.8, 1.5};
+    const double mean = (double)total_rows / g->experts, dev = sqrt(mean), k = g->K / 128.0;
+    int best = kTile64x128;
+    double least = -1.0;
+    for (const Shape& s : shapes[g->bits == 8]) {
+        const int bm = tile_bm(s.variant);
+        double ctas = 0.0, heights = 0.0;           // row tiles, and their 16-row tiles
+        int longest = 0;
+        for (double d : spread) {
+            const int rows = (int)ceil(mean + d * dev > 0.0 ? mean + d * dev : 0.0);
+            const int left = rows % bm, tail = ceil_div(left, 32) * 2;
+            ctas += rows / bm + (left > 0);
+            heights += rows / bm * (bm / 16) + tail;
+            if (rows >= bm) longest = bm / 16;
+            else if (tail > longest) longest = tail;
+        }
+        const double per_cu = g->experts / 7.0 * ceil_div(g->N, tile_bn(s.variant)) / num_cu;
+        ctas *= per_cu;
+        heights *= per_cu;
+        const bool fine = g->group == 32;
+        const double t = ctas <= 1.0 ? s.one[0] + k * (s.one[1] + s.one[2] * longest + s.one[3] * heights + (fine ? s.one32 : 0.0))
+                                     : s.more[0] + k * (s.more[1] * ctas + s.more[2] * heights + s.more[3] * ceil(ctas - 0.02) + (fine ? s.more32 * ctas : 0.0));
+        if (least < 0.0 || t < least) {
+            least = t;
+            best = s.variant;
+        }
+    }
+    return best;
+}
+
 // Kernel choice for the grouped launch.  The rows per expert live on the device, so the row-tile height comes from
 // the average load (total_rows / experts) and the strip width from how many strips the experts that can be active
 // need to cover the chip; wide strips reuse each activation fragment for more weights.
@@ -172,12 +222,19 @@ void grouped_plan(const tm_expert_group* g, int total_rows, int num_cu, int* var
     const int active = total_rows < g->experts ? total_rows : g->experts;
     const int want = ceil_div(2 * num_cu, active > 0 ? active : 1);         // strips per expert for two CTAs per CU
     int per = NT / (want > NT ? NT : want);                                  // tiles per strip, at least one
+    const bool tiles = (uint64_t)total_rows * (uint64_t)g->K < (1ull << 31);        // what the CTA tiles' 32-bit row offsets reach
+    // 17 ... 32 rows: 32 x 128 tiles, which scale the fp32 sums of a group as the decode kernels of that height do.  Those (8 waves that
+    // split K, a ring of registers) stay ahead where K is long, the sooner the finer the groups are: mean of 9 ... 18 rows, 4-bit,
+    // K up to 12288 / 8192 / 4096 at groups of 128 / 64 / 32 1.7 / 1.5 / 1.4 times as fast on tiles (worst twentieth 1.1), 8-bit formats
+    // up to 4096 / 3072 / 2048 1.4 / 1.4 / 1.3 times; at groups of 32 and K above 10000 0.6 ... 0.9 times.
+    const int most_k = g->bits == 4 ? (g->group == 32 ? 4096 : g->group == 64 ? 8192 : 12288) : (g->group == 32 ? 2048 : g->group == 64 ? 3072 : 4096);
     int v;
     if (g_force_variant >= 0) v = g_force_variant;
-    else if (avg > 192) v = kTile128x256;            // prefill-sized loads: CTA tiles, weights read once per row tile
-    else if (avg > 64) v = kTile64x128;
+    else if (avg > 64 || (avg > 32 && tiles)) v = grouped_tile(g, total_rows, num_cu);      // weights read once per row tile
     else if (avg > 32) v = kSkinny64x64;
-    else if (avg > 16) v = kSkinny32x64;
+    // 4-bit experts that fill the chip only with strips of one column tile: the one-shot kernels also for a second pass
+    // (mean of 9 / 12 rows: 0.7 / 0.84 times the time on 32 x 128 tiles, at 16 rows the same)
+    else if (avg > 16 && !(g->bits == 4 && per == 1 && avg <= 24)) v = tiles && g->K <= most_k ? kTile32x128 : kSkinny32x64;
     else v = per >= 8 ? kSkinny16x128 : per >= 4 ? kSkinny16x64 : per >= 2 ? kSkinny16x32 : kSkinny16x16;
     const int ntw = is_skinny(v) ? skinny_ntw(v) : 1;
     if (per > ntw) per = ntw;

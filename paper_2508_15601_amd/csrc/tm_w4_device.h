@@ -152,6 +152,17 @@ __device__ __forceinline__ f16x8 dequant8(uint32_t w, const GroupConst& g, const
     return f16x8{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
 }
 
+// The conversion without its last multiply: q - z, exactly.
+__device__ __forceinline__ f16x8 exact8(uint32_t w, const GroupConst& g, const Magic& mg)
+{
+    const uint32_t w8 = w >> 8;
+    const f16x2 r0 = as_f16x2((w & 0x000F000Fu) | mg.m1024) + g.off1024;
+    const f16x2 r1 = as_f16x2((w & 0x00F000F0u) | mg.m64) + g.off64;
+    const f16x2 r2 = as_f16x2((w8 & 0x000F000Fu) | mg.m1024) + g.off1024;
+    const f16x2 r3 = as_f16x2((w8 & 0x00F000F0u) | mg.m64) + g.off64;
+    return f16x8{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
+}
+
 // The bit-manipulation half of the conversion alone: the eight fp16 values (1024 + q) / (64 + q), alternating in
 // pairs (e0,e1: +1024; e2,e3: +64; e4,e5: +1024; e6,e7: +64), still carrying their conversion bias.
 __device__ __forceinline__ f16x8 biased8(uint32_t w, const Magic& mg)
@@ -205,6 +216,17 @@ __device__ __forceinline__ f16x8 dequant8_w8(uint32_t w0, uint32_t w1, const Gro
     f16x2 r1 = (as_f16x2(__builtin_amdgcn_perm(hi, w0, 0x04030402u)) + g.off1024) * g.s2;
     f16x2 r2 = (as_f16x2(__builtin_amdgcn_perm(hi, w1, 0x04010400u)) + g.off1024) * g.s2;
     f16x2 r3 = (as_f16x2(__builtin_amdgcn_perm(hi, w1, 0x04030402u)) + g.off1024) * g.s2;
+    return f16x8{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
+}
+
+// The same without the multiply.
+__device__ __forceinline__ f16x8 exact8_w8(uint32_t w0, uint32_t w1, const GroupConst& g)
+{
+    const uint32_t hi = 0x64646464u;
+    const f16x2 r0 = as_f16x2(__builtin_amdgcn_perm(hi, w0, 0x04010400u)) + g.off1024;
+    const f16x2 r1 = as_f16x2(__builtin_amdgcn_perm(hi, w0, 0x04030402u)) + g.off1024;
+    const f16x2 r2 = as_f16x2(__builtin_amdgcn_perm(hi, w1, 0x04010400u)) + g.off1024;
+    const f16x2 r3 = as_f16x2(__builtin_amdgcn_perm(hi, w1, 0x04030402u)) + g.off1024;
     return f16x8{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
 }
 

@@ -45,9 +45,34 @@ constexpr int kPanelN = 8;                 // output tiles per panel row (XCD-lo
 // tile_body is one CTA's work on output tile (tile_m, tile_n) and K split sk of one GEMM.
 // FMT is the weight format (kFmtInt4, kFmtInt8, kFmtFp8): 8-bit codes take two words per MFMA step and their packed
 // units hold two steps (64 rows) instead of four.
-template <int TM, int TN, int NW, int GPU, int KW, int PD, int KG, int FMT = kFmtInt4>
-__device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m, const int tile_n, const int sk)
+//
+// The caller provides the two X buffers (TileLds), so that bodies of several heights in one kernel share them: separate
+// objects, so that the compiler can tell a write into one from a read of the other; after the K loop the first also carries the
+// wave sets' partial tiles.
+template <int TM, int TN, int NW, int KW, int KG>
+struct TileLds {
+    static constexpr size_t kXsBytes = (size_t)TM * 16 * 32 * KW * KG * sizeof(uint16_t);
+    // one wave set's partial tile; the sets' tiles meet pairwise (see the end of the K loop), as many at a time as fit
+    static constexpr size_t kSetTileBytes = (size_t)NW * TM * TN * 64 * sizeof(f32x4);
+    // (a tile of more than 64 KiB is handed over in row parts, so that the buffer stays at 64 KiB)
+    static constexpr size_t kRedCap = 64 * 1024;
+    static constexpr int kRedParts = kSetTileBytes > kRedCap ? (int)(kSetTileBytes / kRedCap) : 1;
+    static_assert(KG == 1 || kSetTileBytes <= kRedCap || (kSetTileBytes % kRedCap == 0 && TM % kRedParts == 0), "set tile parts");
+    static constexpr size_t kRedBytes = KG > 1 ? kSetTileBytes / kRedParts : 0;
+    static constexpr size_t kFirst = kXsBytes > kRedBytes ? kXsBytes : kRedBytes;
+};
+
+// m0: first row of the CTA's tile.
+//
+// SUMS: the scales are applied to the fp32 sums of every group instead of to the weights, which so enter the matrix cores as
+// the exact differences q - z (FP8: the exact codes).  That saves the four multiplies of a conversion and costs 4 * TM * TN
+// multiply-adds a group: at 32 rows and groups of 128, 22 instead of 26 vector instructions a step.  It is the precision of the
+// decode kernels up to 32 rows.
+template <int TM, int TN, int NW, int GPU, int KW, int PD, int KG, int FMT = kFmtInt4, bool SUMS = false>
+__device__ __forceinline__ void tile_body(const GemmParams& p, const int m0, const int tile_m, const int tile_n, const int sk,
+                                          unsigned char* smem0, unsigned char* smem1)
 {
+    using Lds = TileLds<TM, TN, NW, KW, KG>;
     constexpr int WPS = FMT == kFmtInt4 ? 1 : 2;           // packed words per lane and MFMA step
     constexpr int SPU = FMT == kFmtInt4 ? 4 : 2;           // MFMA steps per packed unit
     constexpr int NT_ = NW * KG * 64;                      // threads per CTA
@@ -59,18 +84,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     constexpr int SG = (KW * GPU) / 4 > 0 ? (KW * GPU) / 4 : 1;   // K-groups touched by one stage
     constexpr int UW = KW > SPU ? KW / SPU : 1;            // packed units touched by one stage
     constexpr int WPU = (KW > SPU ? SPU : KW) * WPS;       // words of a unit used by one stage
-    // two X buffers, separate objects so that the compiler can tell a write into one from a read of the other;
-    // after the K loop the first also carries the wave sets' partial tiles
-    constexpr size_t kXsBytes = (size_t)BM * BKS * sizeof(uint16_t);
-    // one wave set's partial tile; the sets' tiles meet pairwise (see the end of the K loop), as many at a time as fit
-    constexpr size_t kSetTileBytes = (size_t)NW * TM * TN * 64 * sizeof(f32x4);
-    // (a tile of more than 64 KiB is handed over in row parts, so that the buffer stays at 64 KiB)
-    constexpr size_t kRedCap = 64 * 1024;
-    constexpr int kRedParts = kSetTileBytes > kRedCap ? (int)(kSetTileBytes / kRedCap) : 1;
-    static_assert(kSetTileBytes <= kRedCap || (kSetTileBytes % kRedCap == 0 && TM % kRedParts == 0), "set tile parts");
-    constexpr size_t kRedBytes = KG > 1 ? kSetTileBytes / kRedParts : 0;
-    __shared__ __attribute__((aligned(16))) unsigned char smem0[kXsBytes > kRedBytes ? kXsBytes : kRedBytes];
-    __shared__ __attribute__((aligned(16))) unsigned char smem1[kXsBytes];
+    constexpr size_t kSetTileBytes = Lds::kSetTileBytes;
+    constexpr int kRedParts = Lds::kRedParts;
     __shared__ uint32_t s_last;
 
     const int tid = threadIdx.x;
@@ -80,7 +95,6 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     const int c = lane & 15, h = lane >> 4;
     const Magic mg = make_magic();
 
-    const int m0 = tile_m * BM;
     const int nt_end = min(p.NT, (tile_n + 1) * (BN / 16));    // 16-column tiles of this CTA end here
     const int nt0 = (tile_n * BN) / 16 + wave * TN;        // first 16-column tile of this wave
     // stages of this CTA's K range (the host makes ku_per_split a multiple of UW when KW > 4)
@@ -153,6 +167,10 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     const uint32_t w_lane = (uint32_t)lane * 16u, sz_lane = (uint32_t)c * 4u;
     uint32_t wset[PD + 1][TN][KW * WPS];
     uint32_t sset[PD + 1][TN][SG];
+    // SUMS: the words of the four columns 4h .. 4h + 3 whose sums the lane holds, of the stage at hand
+    static_assert(!SUMS || (KW * GPU >= 4 && TM <= 4), "a stage holds whole groups");
+    u32x4 quads[SUMS ? TN : 1][SUMS ? SG : 1];
+    const uint32_t q_lane = (uint32_t)h * 16u;
     // one descriptor per 16-column tile of this wave: its K/128 packed units, and its K/group scale/zero rows.
     // A tile past the edge of the strip gets empty descriptors: its loads return zero without touching memory
     // (its results are never stored), which keeps the K loop free of branches.
@@ -164,13 +182,15 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
         w_rsrc[j] = make_rsrc((const char*)p.W + (size_t)nt * p.KU * 1024, live ? (uint32_t)p.KU * 1024u : 0u);
         s_rsrc[j] = make_rsrc((const char*)p.SZ + (size_t)nt * p.G * 64, live ? (uint32_t)p.G * 64u : 0u);
     }
-    auto load_w = [&](uint32_t (&w)[TN][KW * WPS], uint32_t (&s)[TN][SG], int stage) {
+    auto load_w = [&](int set, int stage) {                // (set: a compile-time constant)
+        auto& w = wset[set];
+        auto& s = sset[set];
         const int st = stage * KG + kg;                    // this wave set's slice of the stage
         // packed unit of the slice, and the first of the lane's four words in it (non-zero only for KW == 2)
         const int wbyte = ((st * KW) / SPU) * 1024 + ((st * KW) % SPU) * 4 * WPS;
         const int grp0 = (st * KW * GPU) / 4;              // first K-group of the slice
         // Issue order = order of first use one or two stages later (the load counter retires in order): the
-        // scale/zero words, then the weights.  (The X loads of a stage are issued before this call.)
+        // scale/zero words, then the weights.  (The X loads of a stage, and its quads, are issued before this call.)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -195,6 +215,14 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
         }
     };
 
+    auto load_quads = [&](int stage) {
+        const int grp0 = ((stage * KG + kg) * KW * GPU) / 4;
+#pragma unroll
+        for (int j = 0; j < (SUMS ? TN : 0); ++j)
+#pragma unroll
+            for (int g = 0; g < SG; ++g) quads[j][g] = __builtin_amdgcn_raw_buffer_load_b128(s_rsrc[j], q_lane, (grp0 + g) * 64, 0);
+    };
+
     // One 32-deep MFMA step over the whole CTA-row tile, software-pipelined as in paper Sec. 4.3: while the
     // matrix cores consume the converted fragments `cur`, the vector ALU converts the fragments of the NEXT step
     // into `nxt`, a few at a time between groups of MFMAs, and LDS reads run one row-pair ahead of their use.
@@ -203,7 +231,11 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     // The fp16 operand of MFMA step tt from the stage's packed words (paper Sec. 3.1 step (iii)).
     auto convert = [&](const uint32_t (&wj)[KW * WPS], int tt, uint32_t szw) -> f16x8 {
         const GroupConst gc = make_group_const(szw);
-        if constexpr (FMT == kFmtInt4) {
+        if constexpr (SUMS) {
+            if constexpr (FMT == kFmtInt4) return exact8(wj[tt], gc, mg);
+            else if constexpr (FMT == kFmtInt8) return exact8_w8(wj[2 * tt], wj[2 * tt + 1], gc);
+            else return cvt8_fp8(wj[2 * tt], wj[2 * tt + 1]);
+        } else if constexpr (FMT == kFmtInt4) {
             return dequant8(wj[tt], gc, mg);
         } else if constexpr (FMT == kFmtInt8) {
             return dequant8_w8(wj[2 * tt], wj[2 * tt + 1], gc);
@@ -246,13 +278,29 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     constexpr bool XAHEAD = TM <= 4;
     constexpr int XF = XAHEAD ? TM : 1;
     f16x8 xfa[XF], xfb[XF];
+    // the sums of the group at hand and of the one before it, which is folded in after the next group's first products have been
+    // issued (a product's result is not there for the instruction right behind it); a stage's last group is folded at once
+    f32x4 part[SUMS && SG > 1 ? 2 : 1][SUMS ? TM : 1][SUMS ? TN : 1];
+    auto fold = [&](int g) {
+#pragma unroll
+        for (int j = 0; j < (SUMS ? TN : 0); ++j) {
+            const u32x4 w = quads[j][g];
+#pragma unroll
+            for (int i = 0; i < XF; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[i][j][r] = __builtin_fmaf((float)as_f16x2(w[r]).x, part[g & (SG > 1 ? 1 : 0)][i][j][r], acc[i][j][r]);
+        }
+    };
     auto read_x = [&](f16x8 (&xf)[XF], int buf, int tt) {
 #pragma unroll
         for (int i = 0; i < XF; ++i) xf[i] = *x_frag(buf, tt, i);
     };
     auto step_ahead = [&](const f16x8 (&xc)[XF], f16x8 (&xn)[XF], int buf, int tt_x_next, const f16x8 (&cur)[TN],
                           f16x8 (&nxt)[TN], const uint32_t (&wsrc)[TN][KW * WPS], const uint32_t (&ssrc)[TN][SG],
-                          int tt_next) {
+                          int tt_next, int tt) {
+        constexpr int TG = 4 / GPU;                        // steps per group
+        (void)tt;
         if (tt_x_next >= 0) read_x(xn, buf, tt_x_next);
 #pragma unroll
         for (int i = 0; i < XF; ++i) {
@@ -261,7 +309,18 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
                 if (j * XF / TN == i)              // spread the TN conversions over the rows
                     nxt[j] = convert(wsrc[j], tt_next, ssrc[j][(tt_next * GPU) / 4 % SG]);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = mfma16x16x32(cur[j], xc[i], acc[i][j]);
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (SUMS) {
+                    f32x4& sum = part[tt / TG & (SG > 1 ? 1 : 0)][i][j];
+                    sum = mfma16x16x32(cur[j], xc[i], tt % TG == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum);
+                } else {
+                    acc[i][j] = mfma16x16x32(cur[j], xc[i], acc[i][j]);
+                }
+            }
+        }
+        if constexpr (SUMS) {
+            if (tt % TG == 0 && tt > 0) fold(tt / TG - 1);
+            if (tt == KW - 1) fold(SG - 1);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -275,7 +334,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
         // order) means the X of the next stage has landed in LDS while the weight prefetch stays in flight across
         // the barrier.  A plain barrier instruction, not __syncthreads(): the fence in the latter waits for every
         // outstanding direct-to-LDS load, i.e. for everything younger in the queue as well.
-        constexpr int kWLoads = TN * SG + TN * UW;
+        constexpr int kWLoads = TN * SG + TN * UW, kQLoads = SUMS ? TN * SG : 0;
         auto stage_barrier = [&](auto NLOADS) {
             // the counter field has 6 bits; a smaller bound only waits for a few weight loads more
             constexpr int n = decltype(NLOADS)::value < 63 ? decltype(NLOADS)::value : 63;
@@ -285,10 +344,10 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
         };
         load_x(0, st0);
         __builtin_amdgcn_sched_barrier(0);                 // nothing may be scheduled across: the count above is exact
-        load_w(wset[0], sset[0], st0);
+        load_w(0, st0);
         static_for<1, PD>([&](auto R) {
             constexpr int r = decltype(R)::value;
-            load_w(wset[r % (PD + 1)], sset[r % (PD + 1)], min(st0 + r, last));
+            load_w(r % (PD + 1), min(st0 + r, last));
         });
 #pragma unroll
         for (int j = 0; j < TN; ++j) wfa[j] = convert(wset[0][j], 0, sset[0][j][0]);
@@ -309,7 +368,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
                     // reading before the barrier that ended the previous stage; these loads come first
                     load_x(buf ^ 1, min(st0 + r + 1, last));
                     __builtin_amdgcn_sched_barrier(0);
-                    load_w(wset[wf], sset[wf], min(st0 + r + PD, last));
+                    load_quads(st0 + r);
+                    load_w(wf, min(st0 + r + PD, last));
                     // The group constants derive from the scale/zero words alone, so the compiler would compute
                     // them right after the load that fetches those words, i.e. wait for loads just issued.  The
                     // words of the NEXT stage are therefore made opaque right before the stage's last step, the
@@ -323,12 +383,12 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
 #pragma unroll
                     for (int tt = 0; tt < KW; tt += 2) {
                         if constexpr (XAHEAD) {
-                            step_ahead(xfa, xfb, buf, tt + 1, wfa, wfb, wset[wi], sset[wi], tt + 1);
+                            step_ahead(xfa, xfb, buf, tt + 1, wfa, wfb, wset[wi], sset[wi], tt + 1, tt);
                             if (tt + 2 < KW) {
-                                step_ahead(xfb, xfa, buf, tt + 2, wfb, wfa, wset[wi], sset[wi], tt + 2);
+                                step_ahead(xfb, xfa, buf, tt + 2, wfb, wfa, wset[wi], sset[wi], tt + 2, tt + 1);
                             } else {
                                 pin_next_sz();
-                                step_ahead(xfb, xfa, buf, -1, wfb, wfa, wset[wn], sset[wn], 0);
+                                step_ahead(xfb, xfa, buf, -1, wfb, wfa, wset[wn], sset[wn], 0, tt + 1);
                             }
                         } else {
                             step(buf, tt, wfa, wfb, wset[wi], sset[wi], tt + 1);
@@ -340,7 +400,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
                             }
                         }
                     }
-                    stage_barrier(std::integral_constant<int, kWLoads>{});
+                    stage_barrier(std::integral_constant<int, kQLoads + kWLoads>{});
                 }
             });
         }
@@ -354,7 +414,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int tile_m,
     if constexpr (KG > 1) {
         f32x4* red = (f32x4*)smem0;
         constexpr int kSetRegs = NW * TM * TN * 64;                    // f32x4 slots of one set's tile
-        constexpr int kCapRaw = (int)(sizeof(smem0) / kSetTileBytes);
+        constexpr int kCapRaw = (int)(Lds::kFirst / kSetTileBytes);
         static_for<0, 3>([&](auto R) {                                 // up to three halvings: KG = 2, 4 or 8
             constexpr int active = KG >> decltype(R)::value;
             if constexpr (active > 1 && kRedParts > 1) {
@@ -532,7 +592,10 @@ __global__ __launch_bounds__(NW * KG * 64) void tile_kernel(GemmParams p)
     const int within = logical % panel_tiles;
     const int pw = min(kPanelN, p.tiles_n - panel * kPanelN);      // width of this panel
     const int tile_m = within / pw, tile_n = panel * kPanelN + within % pw;
-    tile_body<TM, TN, NW, GPU, KW, PD, KG, FMT>(p, tile_m, tile_n, sk);
+    using Lds = TileLds<TM, TN, NW, KW, KG>;
+    __shared__ __attribute__((aligned(16))) unsigned char smem0[Lds::kFirst];
+    __shared__ __attribute__((aligned(16))) unsigned char smem1[Lds::kXsBytes];
+    tile_body<TM, TN, NW, GPU, KW, PD, KG, FMT>(p, tile_m * (TM * 16), tile_m, tile_n, sk, smem0, smem1);
 }
 
 // KW8: stages two packed units deep (needs an even number of units per K split, which the host checks);

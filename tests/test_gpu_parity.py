@@ -942,6 +942,51 @@ def test_grouped_gemm_8bit_formats_against_oracle(tm, oracle, E, K, N, g, counts
         p.close()
 
 
+# row tiles that an expert does not fill run as tiles of 32, 64 or 96 rows: every height at its edges, over more than 64 experts too, and more
+# row tiles than fit one round; 32 x 128 tiles scale the sums of one, two and four groups per stage
+GROUPED_TAIL_CASES = [
+    # E, K, N, g, rows per expert
+    (12, 256, 272, 128, [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 0, 225]),
+    (9, 384, 144, 64, [32, 0, 63, 95, 127, 160, 161, 192, 193]),
+    (7, 128, 528, 32, [33, 97, 0, 65, 1, 130, 256]),
+    (70, 256, 96, 128, [0] * 20 + [34] + [2] * 30 + [100, 66] + [1] * 17),
+    (5, 512, 16, 64, [0, 0, 0, 0, 40]),
+]
+
+
+@pytest.mark.parametrize("fmt", ["int4", "int8", "fp8"])
+@pytest.mark.parametrize("variant", [13, 9, 7])            # 32 x 128, 64 x 128, 128 x 256
+@pytest.mark.parametrize("E,K,N,g,counts", GROUPED_TAIL_CASES)
+def test_grouped_gemm_row_tile_heights(tm, oracle, E, K, N, g, counts, variant, fmt):
+    if fmt == "int4":
+        test_grouped_gemm_against_oracle(tm, oracle, E, K, N, g, counts, 2, 3, variant)
+    else:
+        test_grouped_gemm_8bit_formats_against_oracle(tm, oracle, E, K, N, g, counts, 2, 3, variant, fmt)
+
+
+@pytest.mark.parametrize("bits,E,K,N,g,rows,name", [
+    (4, 8, 256, 1024, 128, 8 * 9, "skinny16x16"),         # strips of one column tile: a second pass of the one-shot kernels
+    (4, 32, 256, 4096, 128, 32 * 9, "tile32x128"),
+    (4, 32, 256, 4096, 32, 32 * 18, "tile32x128"),
+    (4, 32, 4224, 1024, 32, 32 * 18, "skinny32x64"),      # long K in fine groups
+    (8, 32, 2048, 1024, 32, 32 * 12, "tile32x128"),
+    (8, 32, 2176, 1024, 32, 32 * 12, "skinny32x64"),
+    (4, 8, 256, 1024, 128, 8 * 40, "tile64x128"),
+    (4, 8, 4096, 7168, 128, 8 * 700, "tile128x256"),
+])
+def test_grouped_gemm_shape_rule(tm, bits, E, K, N, g, rows, name):
+    """Which kernel the mean load of the experts asks for on 256 CUs."""
+    rng = np.random.default_rng(K + rows)
+    if bits == 4:
+        _, dev = _make_experts(tm, rng, 1, K, N, g)
+    else:
+        dev = [_pack_w8(tm, *_w8_case(rng, K, N, g), g)]
+    group = tm.tm_group_experts(dev * E)
+    assert tm.tm_variant_name(tm.tm_get_grouped_plan(group, rows)[0]) == name
+    group.close()
+    dev[0].close()
+
+
 def test_grouped_gemm_rejects_mixed_formats(tm, oracle):
     rng = np.random.default_rng(9)
     _, dev4 = _make_experts(tm, rng, 1, 256, 32, 128)
