@@ -570,6 +570,54 @@ static void weigh_tile_shape_and_split(const tm_packed_w4* h, int M, int num_cu,
     }
 }
 
+// Unsplit launches of 4-bit layers above 64 rows: the shape chosen so far (128 x 256, 128 x 128 or 64 x 128) against two that the
+// rules above do not weigh, 64 x 96 and 64 x 128 with one wave set per CTA.  Their CTAs of four waves share a CU by three or four, so a
+// launch of several CTAs per CU ends more evenly and hides a CTA's start and end behind the others.  The estimate is a least-squares
+// fit to timed unsplit plans of 7138 random layers (K 1024 ... 28672, N 1024 ... 32768, M 65 ... 4096, every group; rms error 3-5 %): a
+// fixed part and, per 128 rows of K, of launches of at most one CTA per CU a part and one by the load, of larger ones parts by the
+// load, by whole rounds of one and of two CTAs per CU; more where groups of 32 make four times the scales, and the output's store.
+// One of the two is taken where it is 5 % ahead: one launch in four, 11 % faster on average (K = 4096, N = 22016, M = 256: 58 us on
+// 128 x 256 tiles, 54 on 64 x 128 in one set), half a per cent of the launches slower.  True: 64 x 128 with one wave set.
+static bool lighter_tile(const tm_packed_w4* h, int M, int num_cu, int& variant)
+{
+    struct Shape {
+        int variant;
+        double one[4];                  // us: fixed; per 128 rows of K: always, by the load, in groups of 32
+        double more[6];                 // fixed; per 128 rows of K: by the load, per round, per round of two, in groups of 32 by the load; output
+    };
+    static const Shape chosen[3] = {
+        {kTile128x256, {9.164, 1.025, 0.629, 0.075}, {6.989, 0.613, 0.827, 0.353, 0.045, 0.314}},
+        {kTile128x128, {6.121, 0.648, 0.260, 0.061}, {4.379, 0.286, 0.479, 0.204, 0.052, 0.396}},
+        {kTile64x128, {4.647, 0.413, 0.117, 0.057}, {3.275, 0.118, 0.398, 0.0, 0.042, 0.837}}};
+    static const Shape other[2] = {
+        {kTile64x96, {4.450, 0.420, 0.056, 0.063}, {4.128, 0.085, 0.287, 0.037, 0.019, 0.627}},
+        {kTile64x128, {4.071, 0.480, 0.105, 0.134}, {4.390, 0.103, 0.390, 0.0, 0.040, 0.246}}};
+    auto estimate = [&](const Shape& s) {
+        const long ctas = (long)ceil_div(M, tile_bm(s.variant)) * ceil_div(h->N, tile_bn(s.variant));
+        const double load = (double)ctas / num_cu, k = h->K / 128.0, fine = h->group == 32 ? 1.0 : 0.0;
+        if (ctas <= num_cu) return s.one[0] + k * (s.one[1] + s.one[2] * load + s.one[3] * fine);
+        const double rounds = (double)((ctas + num_cu - 1) / num_cu), twos = (double)((ctas + 2L * num_cu - 1) / (2L * num_cu));
+        return s.more[0] + k * (s.more[1] * load + s.more[2] * rounds + s.more[3] * twos + s.more[4] * fine * load) +
+               s.more[5] * ctas * tile_bm(s.variant) * tile_bn(s.variant) * 1e-6;
+    };
+    for (const Shape& c : chosen) {
+        if (c.variant != variant) continue;
+        double least = 0.95 * estimate(c);
+        const Shape* best = nullptr;
+        for (const Shape& o : other) {
+            const double t = estimate(o);
+            if (t < least) {
+                least = t;
+                best = &o;
+            }
+        }
+        if (!best) return false;
+        variant = best->variant;
+        return variant == kTile64x128;
+    }
+    return false;
+}
+
 Plan make_plan(const tm_packed_w4* h, int M, int num_cu)
 {
     // packed units along K: 128 rows of 4-bit codes or 64 rows of 8-bit codes (1 KiB per 16 columns either way)
@@ -585,6 +633,7 @@ Plan make_plan(const tm_packed_w4* h, int M, int num_cu)
         variant = M <= 32 ? kSkinny32x64 : (M <= 64 ? kSkinny64x64 : (w8 ? kTile64x128 : kTile64x256));
     pl.variant = variant;
     int split = 1;
+    bool one_set = false;
     if (is_skinny(variant)) {
         const int ntw = skinny_ntw(variant);
         // fewest strips the variant can take; when chosen automatically for M <= 16 that is one strip per CU
@@ -667,6 +716,12 @@ Plan make_plan(const tm_packed_w4* h, int M, int num_cu)
             }
         }
         weigh_tile_shape_and_split(h, M, num_cu, KU, variant, split, pl);
+        if (!w8 && M > 64 && split == 1 && g_force_variant < 0 && g_force_split == 0 && g_force_waves == 0 && g_force_stage == 0) {
+            one_set = lighter_tile(h, M, num_cu, variant);
+            pl.variant = variant;
+            pl.tiles_m = ceil_div(M, tile_bm(variant));
+            pl.tiles_n = ceil_div(h->N, tile_bn(variant));
+        }
     }
     if (g_force_split > 0) split = g_force_split;
     if (pl.tiles_m * pl.tiles_n > kMaxCounters) split = 1;     // one arrival counter per output tile
@@ -699,11 +754,12 @@ Plan make_plan(const tm_packed_w4* h, int M, int num_cu)
         if (tile_two_waves(variant)) kg = tile_bn(variant) == 96 ? 2 : 4;
         // (64-row tiles: two sets with 128-deep stages measured ahead of four sets with 64-deep ones, 40.2 against
         // 42.0 us at K = N = 8192, M = 256)
-        else if (bm <= 64 && (long)pl.tiles_m * pl.tiles_n * split < 2L * num_cu) kg = bm == 64 ? 2 : 4;
+        else if (bm <= 64 && !one_set && (long)pl.tiles_m * pl.tiles_n * split < 2L * num_cu) kg = bm == 64 ? 2 : 4;
         // (128-row tiles with at most one CTA per CU: two sets, 7-14 % faster than one - K = N = 8192, M = 384: 60 against
         // 70 us on 192 tiles of 128 x 128; slower once CTAs run in two rounds, K = 4096, N = 28672, M = 256: 72 against 64 us)
         else if ((variant == kTile128x128 || variant == kTile128x256) && (long)pl.tiles_m * pl.tiles_n * split <= num_cu) kg = 2;
-        if (bm <= 64 && kg > 1 && g_force_stage <= 1) steps = 4;
+        // (64 x 128 in one set: three CTAs share a CU with 128-deep stages, two with 256-deep ones: 2-5 % faster above two CTAs per CU)
+        if (((bm <= 64 && kg > 1) || variant == kTile64x128) && g_force_stage <= 1) steps = 4;
         if (g_force_waves >= 4) kg = g_force_waves * 64 / tile_threads(variant);
         if (!tile_has_kgroups(variant, kg)) kg = tile_has_kgroups(variant, 1) ? 1 : 4;
         if (w8) {

@@ -220,6 +220,28 @@ def test_integer_exact_case(tm, oracle, M, variant, split):
     assert np.array_equal(Y.view(np.uint16), Yref.view(np.uint16))
 
 
+@pytest.mark.parametrize("M,K,N,g,name,block", [
+    (210, 1280, 10480, 64, "tile64x96", 256),
+    (473, 2688, 4144, 128, "tile64x96", 256),        # an odd number of packed units: 64-deep stages
+    (139, 1920, 16496, 128, "tile64x128", 256),      # one wave set
+    (100, 1024, 16384, 32, "tile64x128", 512),       # one CTA per CU: two
+    (1024, 1024, 8192, 128, "tile128x256", 512),     # the same of the larger tile
+])
+def test_tile_shape_of_several_ctas_per_cu(tm, oracle, M, K, N, g, name, block):
+    """Unsplit launches above 64 rows: which tile the estimates ask for on 256 CUs, and that it is right (sampled rows, the edges of
+    the row tiles among them)."""
+    d = _random_problem(M + K, M, K, N, g)
+    packed = gu.pack(d, g)
+    plan = tm.tm_get_plan(packed, M)
+    _say(f"M={M} K={K} N={N} g={g} plan={plan}")
+    assert (plan["name"], plan["split_k"], plan["block"]) == (name, 1, block)
+    Y = gu.gemm(packed, d["X"])
+    rows = sorted({0, 15, 16, 63, 64, M // 2, M - 2, M - 1})
+    ok, worst, fro = acceptance(Y[rows], oracle.gemm(d["X"][rows], d["q"], d["s"], d["z"], g))
+    assert ok, (worst, fro)
+    packed.close()
+
+
 # The two prefill tiles exist with the 16x16x32 and with the 32x32x16 matrix instruction (the latter on request only):
 # both forms of both tiles, exact cases first.
 @pytest.mark.parametrize("shape", [16, 32])
