@@ -160,12 +160,12 @@ int ceil_div(int a, int b);
 
 // The CTA tile of a grouped launch, 64 x 128 or 128 x 256, from an estimate of both.  The rows per expert live on the device; a
 // balanced routing spreads them like counts of that mean, of which seven values stand for all experts.  A row tile that an
-// expert does not fill runs as one of 32, 64 or 96 rows.  The estimate is a least-squares fit to timed launches (4-bit: 3594, 8-bit
-// formats: 5421; 4 ... 128 experts, K and N 1024 ... 14336 x 28672, mean 6 ... 700 rows, every group): a fixed part and, per 128
+// expert does not fill runs as one of 32, 64 or 96 rows.  The estimate is a least-squares fit to launches timed on both in turn (4-bit:
+// 2198, 8-bit formats: 1624; 4 ... 96 experts, K and N 1024 ... 14336 x 28672, mean 20 ... 900 rows, every group): a fixed part and, per 128
 // rows of K, of launches of at most one CTA per CU a part per CTA, per 16 rows of the longest CTA and per 16 rows and CU, of larger ones a
-// part per CTA and CU, per 16 rows and CU, and per round.  Its choices are 1.1 % (64 ... 800 rows) to 4 % (below) behind the faster
-// of the two on average, where 64 x 128 throughout is 9-16 % behind above 64 rows and 128 x 256 throughout 6-30 %: 8 experts of
-// 4096 x 28672 and 14336 x 4096, 250 rows: 565 + 343 us on 128 x 256 tiles, 547 + 281 on 64 x 128; 1000 rows of 4096 x 7168: 437 and 480.
+// part per CTA and CU, per 16 rows and CU, and per round.  On as many others its choices are 0.2-2 % behind the faster of the two on
+// average (8-bit formats 1-3 %); 64 x 128 throughout is 3-7 % behind above 64 rows (8-10 %), 128 x 256 throughout 7-33 % (6-18 %).
+// 8 experts, 250 rows: 14336 x 4096 281 us on 64 x 128 tiles, 338 on 128 x 256; 1000 rows of 4096 x 7168: 480 and 437.
 int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
 {
     struct Shape {
@@ -174,10 +174,10 @@ int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
         double one32, more32;           // groups of 32: more per 128 rows of K
     };
     static const Shape shapes[2][2] = {
-        {{kTile64x128, {3.76, 0.289, 0.065, 0.033}, {4.56, 0.149, 0.073, 0.194}, 0.114, 0.049},
-         {kTile128x256, {5.03, 0.665, 0.109, 0.073}, {7.05, 0.0, 0.183, 0.597}, 0.108, 0.081}},
-        {{kTile64x128, {3.63, 0.292, 0.042, 0.072}, {3.18, 0.487, 0.0, 0.216}, 0.061, 0.069},
-         {kTile128x256, {4.07, 0.566, 0.099, 0.128}, {2.40, 0.834, 0.097, 0.481}, 0.129, 0.229}}};
+        {{kTile64x128, {4.242, 0.283, 0.061, 0.032}, {6.128, 0.140, 0.062, 0.227}, 0.115, 0.044},
+         {kTile128x256, {5.902, 0.580, 0.107, 0.104}, {9.803, 0.061, 0.172, 0.681}, 0.107, 0.053}},
+        {{kTile64x128, {4.254, 0.285, 0.047, 0.055}, {5.065, 0.407, 0.0, 0.263}, 0.077, 0.060},
+         {kTile128x256, {4.879, 0.502, 0.104, 0.141}, {8.498, 0.567, 0.127, 0.593}, 0.105, 0.248}}};
     static const double spread[7] = {-1.5, -0.8, -0.4, 0.0, 0.4, 0.8, 1.5};
     const double mean = (double)total_rows / g->experts, dev = sqrt(mean), k = g->K / 128.0;
     int best = kTile64x128;
