@@ -23,6 +23,10 @@ UNITS = {"tm_w4_tile_small": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "tm_w4_tile_w8": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "tm_w4_tile_large": [],
          "tm_w4_tile32": []}
+# barrier-terminated regions with direct-to-LDS loads that a unit has at least (a prologue and the unrolled stages of every body)
+REGIONS = {"tm_w4_tile_small": 300, "tm_w4_tile_kgroup": 560, "tm_w4_tile_grouped": 420, "tm_w4_tile_w8": 360,
+           "tm_w4_tile_large": 36, "tm_w4_tile32": 40}
+KERNEL = r"_ZN4tmw4[^\n]*tile(?:32|_grouped)?_kernel[^\n]*"
 VMCNT_MAX = 63          # six-bit counter: a wave cannot have more loads outstanding, so a larger bound is no wait at all
 
 
@@ -37,7 +41,7 @@ def _assembly(unit, extra, outdir):
 
 def _stage_regions(text):
     """(kernel name, instructions of one barrier-terminated region) for every region that loads into LDS."""
-    for m in re.finditer(r"^(_ZN4tmw4[^\n]*tile(?:32)?_kernel[^\n]*):\s*;[^\n]*\n(.*?)^\.Lfunc_end", text, re.S | re.M):
+    for m in re.finditer(rf"^({KERNEL}):\s*;[^\n]*\n(.*?)^\.Lfunc_end", text, re.S | re.M):
         region = []
         for line in m.group(2).splitlines():
             t = line.strip()
@@ -50,12 +54,20 @@ def _stage_regions(text):
                 region = []
 
 
-@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not available")
-def test_stage_end_wait_covers_the_direct_to_lds_loads(tmp_path):
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """Unit -> its assembly."""
+    if shutil.which(HIPCC) is None:
+        pytest.skip("hipcc not available")
+    outdir = str(tmp_path_factory.mktemp("isa"))
     with concurrent.futures.ThreadPoolExecutor(max_workers=3) as pool:
-        texts = list(pool.map(lambda kv: _assembly(kv[0], kv[1], str(tmp_path)), UNITS.items()))
-    checked = 0
-    for text in texts:
+        return dict(zip(UNITS, pool.map(lambda kv: _assembly(kv[0], kv[1], outdir), UNITS.items())))
+
+
+def test_stage_end_wait_covers_the_direct_to_lds_loads(assembly):
+    assert set(assembly) == set(REGIONS)
+    for unit, text in assembly.items():
+        checked = dict.fromkeys(re.findall(rf"^({KERNEL}):\s*;", text, re.M), 0)
         for name, reg in _stage_regions(text):
             is_load = [t.startswith("buffer_load") for t in reg]
             is_lds = [ld and t.endswith("lds") for ld, t in zip(is_load, reg)]
@@ -77,5 +89,6 @@ def test_stage_end_wait_covers_the_direct_to_lds_loads(tmp_path):
             ds = [i for i, t in enumerate(reg) if t.startswith("ds_read")]
             if ds:
                 assert any(t.startswith("s_waitcnt") and "lgkmcnt(0)" in t for t in reg[ds[-1] + 1:]), (name, "LDS reads")
-            checked += 1
-    assert checked > 1200        # every instantiation has a prologue and PD*(PD+1) unrolled stages
+            checked[name] += 1
+        # every kernel has a prologue and PD*(PD+1) >= 2 unrolled stages
+        assert min(checked.values()) >= 3 and sum(checked.values()) >= REGIONS[unit], (unit, checked)
