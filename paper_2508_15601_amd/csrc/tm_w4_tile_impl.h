@@ -166,6 +166,9 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int m0, con
     // packed weights and scale/zero words of stage r live in register set r % (PD + 1)
     const uint32_t w_lane = (uint32_t)lane * 16u, sz_lane = (uint32_t)c * 4u;
     uint32_t wset[PD + 1][TN][KW * WPS];
+    // (exact FP8 codes need no word of their group: nothing would use the loads, so the compiler might drop some of them, and the
+    // waits that count them would let loads into LDS run on)
+    constexpr bool kPairs = !(SUMS && FMT == kFmtFp8);
     uint32_t sset[PD + 1][TN][SG];
     // SUMS: the words of the four columns 4h .. 4h + 3 whose sums the lane holds, of the stage at hand
     static_assert(!SUMS || (KW * GPU >= 4 && TM <= 4), "a stage holds whole groups");
@@ -195,7 +198,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int m0, con
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int g = 0; g < SG; ++g)
-                s[j][g] = __builtin_amdgcn_raw_buffer_load_b32(s_rsrc[j], sz_lane, (grp0 + g) * 64, 0);
+                if constexpr (kPairs) s[j][g] = __builtin_amdgcn_raw_buffer_load_b32(s_rsrc[j], sz_lane, (grp0 + g) * 64, 0);
+                else s[j][g] = 0u;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
 #pragma unroll
@@ -334,7 +338,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int m0, con
         // order) means the X of the next stage has landed in LDS while the weight prefetch stays in flight across
         // the barrier.  A plain barrier instruction, not __syncthreads(): the fence in the latter waits for every
         // outstanding direct-to-LDS load, i.e. for everything younger in the queue as well.
-        constexpr int kWLoads = TN * SG + TN * UW, kQLoads = SUMS ? TN * SG : 0;
+        constexpr int kWLoads = (kPairs ? TN * SG : 0) + TN * UW, kQLoads = SUMS ? TN * SG : 0;
         auto stage_barrier = [&](auto NLOADS) {
             // the counter field has 6 bits; a smaller bound only waits for a few weight loads more
             constexpr int n = decltype(NLOADS)::value < 63 ? decltype(NLOADS)::value : 63;
@@ -378,7 +382,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, const int m0, con
 #pragma unroll
                         for (int j = 0; j < TN; ++j)
 #pragma unroll
-                            for (int g = 0; g < SG; ++g) asm volatile("" : "+v"(sset[wn][j][g]));
+                            for (int g = 0; g < SG; ++g)
+                                if constexpr (kPairs) asm volatile("" : "+v"(sset[wn][j][g]));
                     };
 #pragma unroll
                     for (int tt = 0; tt < KW; tt += 2) {

@@ -92,3 +92,12 @@ def test_stage_end_wait_covers_the_direct_to_lds_loads(assembly):
             checked[name] += 1
         # every kernel has a prologue and PD*(PD+1) >= 2 unrolled stages
         assert min(checked.values()) >= 3 and sum(checked.values()) >= REGIONS[unit], (unit, checked)
+
+
+def test_no_load_is_counted_that_nothing_uses(assembly):
+    """The 32-row grouped FP8 kernels multiply exact codes and scale the sums of a group by quads of words: a load of the single
+    words that other conversions take would have no use, and the compiler would be free to drop it from under the waits that count it."""
+    body = re.compile(r"^_ZN4tmw4[^\n]*tile_grouped_kernelILi2E[^\n]*Li18EE[^\n]*:\s*;[^\n]*\n(.*?)^\.Lfunc_end", re.S | re.M)
+    texts = body.findall(assembly["tm_w4_tile_grouped"])
+    assert len(texts) == 3 and all(t.count("buffer_load_dwordx4") > 0 for t in texts)
+    assert not any(re.search(r"^\s*buffer_load_dword v", t, re.M) for t in texts)
