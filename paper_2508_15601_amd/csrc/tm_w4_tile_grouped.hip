@@ -95,11 +95,26 @@ __global__ __launch_bounds__(NW * 64) void tile_grouped_kernel(GroupedParams gp)
     __shared__ __attribute__((aligned(16))) unsigned char smem0[Lds::kFirst];
     __shared__ __attribute__((aligned(16))) unsigned char smem1[Lds::kXsBytes];
     const int m0 = tile_m * BM, left = p.M - m0;
-    // the last row tile of an expert: a body of as many rows as are left, in steps of 32
-    if (TM > 2 && left <= 32) tile_body<2, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
-    else if (TM > 4 && left <= 64) tile_body<4, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
-    else if (TM > 6 && left <= 96) tile_body<6, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
-    else tile_body<TM, TN, NW, GPU, KW, PD, 1, FMT, TM == 2>(p, m0, tile_m, tile_n, 0, smem0, smem1);
+    // The last row tile of an expert: a body of as many rows as are left, in steps of 32.  The tallest body comes first in the code:
+    // behind a shorter one it was given two more registers (64 x 128, 4-bit, groups of 128: 130 instead of 128, three CTAs per CU
+    // instead of four; int8 in groups of 32: 170 instead of 168, two instead of three).
+    if (TM == 2 || left > 16 * TM - 32) {
+        tile_body<TM, TN, NW, GPU, KW, PD, 1, FMT, TM == 2>(p, m0, tile_m, tile_n, 0, smem0, smem1);
+        return;
+    }
+    if constexpr (TM > 6) {
+        if (left > 64) {
+            tile_body<6, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
+            return;
+        }
+    }
+    if constexpr (TM > 4) {
+        if (left > 32) {
+            tile_body<4, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
+            return;
+        }
+    }
+    if constexpr (TM > 2) tile_body<2, TN, NW, GPU, KW, PD, 1, FMT>(p, m0, tile_m, tile_n, 0, smem0, smem1);
 }
 
 template <int TM, int TN, int KW, int FMT = kFmtInt4>

@@ -101,3 +101,17 @@ def test_no_load_is_counted_that_nothing_uses(assembly):
     texts = body.findall(assembly["tm_w4_tile_grouped"])
     assert len(texts) == 3 and all(t.count("buffer_load_dwordx4") > 0 for t in texts)
     assert not any(re.search(r"^\s*buffer_load_dword v", t, re.M) for t in texts)
+
+
+def test_registers_of_the_64_row_grouped_tiles(assembly):
+    """Several bodies in one kernel must not cost a resident CTA: 128 registers are four waves per SIMD, 168 three (of 512, in steps
+    of 8), nothing is spilled, and the fourth CTA's X buffers fit the 160 KiB of LDS."""
+    found = 0
+    for m in re.finditer(r"\.group_segment_fixed_size: (\d+)\n(?:(?!\.group_segment_fixed_size).)*?\.symbol:\s+(\S*tile_grouped_kernelILi4E\S*)\.kd"
+                         r"(?:(?!\.group_segment_fixed_size).)*?\.vgpr_count:\s+(\d+)\n\s+\.vgpr_spill_count: (\d+)",
+                         assembly["tm_w4_tile_grouped"], re.S):
+        lds, name, vgprs, spilled = int(m.group(1)), m.group(2), int(m.group(3)), int(m.group(4))
+        four = "Li1ELi4ELi4EE" in name               # 4-bit codes in groups of 128
+        assert spilled == 0 and 512 // (-(-vgprs // 8) * 8) >= (4 if four else 3) and 4 * lds <= 160 * 1024, (name, vgprs, spilled, lds)
+        found += 1
+    assert found == 9
