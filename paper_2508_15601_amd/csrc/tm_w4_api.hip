@@ -223,18 +223,26 @@ void grouped_plan(const tm_expert_group* g, int total_rows, int num_cu, int* var
     const int want = ceil_div(2 * num_cu, active > 0 ? active : 1);         // strips per expert for two CTAs per CU
     int per = NT / (want > NT ? NT : want);                                  // tiles per strip, at least one
     const bool tiles = (uint64_t)total_rows * (uint64_t)g->K < (1ull << 31);        // what the CTA tiles' 32-bit row offsets reach
-    // 17 ... 32 rows: 32 x 128 tiles, which scale the fp32 sums of a group as the decode kernels of that height do.  Those (8 waves that
-    // split K, a ring of registers) stay ahead where K is long, the sooner the finer the groups are: mean of 9 ... 18 rows, 4-bit,
-    // K up to 12288 / 8192 / 4096 at groups of 128 / 64 / 32 1.7 / 1.5 / 1.4 times as fast on tiles (worst twentieth 1.1), 8-bit formats
-    // up to 4096 / 3072 / 2048 1.4 / 1.4 / 1.3 times; at groups of 32 and K above 10000 0.6 ... 0.9 times.
+    // 17 ... 32 rows: 32 x 128 tiles, which scale the fp32 sums of a group as the decode kernels of that height do, where they fill the
+    // chip.  Those (32 x 64: 8 waves that split K, a ring of registers) stay ahead where K is long, the sooner the finer the groups are:
+    // mean of 9 ... 18 rows, 4-bit, K up to 12288 / 8192 / 4096 at groups of 128 / 64 / 32 1.7 / 1.5 / 1.4 times as fast on tiles (worst
+    // twentieth 1.1), 8-bit formats up to 4096 / 3072 / 2048 1.4 / 1.4 / 1.3 times; at groups of 32 and K above 10000 0.6 ... 0.9 times.
     const int most_k = g->bits == 4 ? (g->group == 32 ? 4096 : g->group == 64 ? 8192 : 12288) : (g->group == 32 ? 2048 : g->group == 64 ? 3072 : 4096);
+    // Up to two 16-column tiles per CU (8-bit formats with 16 rows or more on average: one) a 32 x 128 tile leaves most CUs without a CTA,
+    // and the 16-row kernels, in passes, are fastest (24294 loads of 1 ... 128 experts, all candidates timed in turn: on those concerned 1.70
+    // (4-bit), 1.61 (int8), 1.51 (FP8) times as fast as the tiles or the 32 x 64 kernels, which the rule by K would take; 4 4-bit experts
+    // of 3968 x 1456, 16 rows: 10.2 us in passes, 16.8 on tiles, 20.6 on 32 x 64).  FP8, from 12 rows: the 32 x 64 kernels up to one 16-column tile per CU.
+    const long cols = (long)active * NT;
+    const bool fp8_few = g->fp8 && mean >= 12, passes = !fp8_few && cols <= (g->bits == 4 || mean <= 15 ? 2L : 1L) * num_cu;
+    // 4-bit experts that fill the chip only with strips of one column tile: the same (mean of 9 / 12 rows: 0.7 / 0.84 times the time on
+    // 32 x 128 tiles, at 16 rows the same; above K = 4096, where no one-shot form is built and the ring-buffered 16-row kernels
+    // run, 0.5 times the time on 32 x 64 on average over 603 loads and 0.91 times at most)
+    const bool narrow = g->bits == 4 && per == 1 && avg <= 24;
     int v;
     if (g_force_variant >= 0) v = g_force_variant;
     else if (avg > 64 || (avg > 32 && tiles)) v = grouped_tile(g, total_rows, num_cu);      // weights read once per row tile
     else if (avg > 32) v = kSkinny64x64;
-    // 4-bit experts that fill the chip only with strips of one column tile: the one-shot kernels also for a second pass
-    // (mean of 9 / 12 rows: 0.7 / 0.84 times the time on 32 x 128 tiles, at 16 rows the same)
-    else if (avg > 16 && !(g->bits == 4 && per == 1 && avg <= 24)) v = tiles && g->K <= most_k ? kTile32x128 : kSkinny32x64;
+    else if (avg > 16 && !passes && !narrow) v = tiles && g->K <= most_k && !(fp8_few && cols <= num_cu) ? kTile32x128 : kSkinny32x64;
     else v = per >= 8 ? kSkinny16x128 : per >= 4 ? kSkinny16x64 : per >= 2 ? kSkinny16x32 : kSkinny16x16;
     const int ntw = is_skinny(v) ? skinny_ntw(v) : 1;
     if (per > ntw) per = ntw;

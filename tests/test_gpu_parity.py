@@ -806,6 +806,8 @@ GROUPED_CASES = [
     (8, 1024, 2064, 64, [3, 0, 16, 2, 0, 0, 9, 1], 2, 3, -1),
     (3, 256, 48, 32, [40, 0, 70], 0, 1, -1),            # average load picks the 64-row kernels; 70 rows = two passes
     (3, 256, 48, 32, [40, 0, 70], 1, 0, 0),             # 16-row kernel: five passes for the last expert
+    (4, 512, 272, 128, [32, 16, 17, 5], 1, 2, -1),      # few CTAs: the 16-row kernels, two passes
+    (2, 640, 144, 32, [33, 1], 0, 1, -1),               # and three
     (3, 384, 336, 128, [33, 2, 18], 0, 0, 1),
     (2, 512, 1040, 64, [16, 15], 0, 0, 2),
     (2, 512, 1040, 128, [7, 31], 0, 0, 16),
@@ -908,6 +910,7 @@ GROUPED_8BIT_CASES = [
     (4, 512, 272, 128, [0, 1, 17, 5], 0, 0, -1),
     (8, 1024, 2064, 64, [3, 0, 16, 2, 0, 0, 9, 1], 2, 3, -1),
     (3, 256, 48, 32, [40, 0, 70], 0, 1, -1),
+    (4, 512, 272, 128, [32, 16, 17, 5], 1, 2, -1),      # few CTAs: int8 in two passes of the 16-row kernels, FP8 on 32 x 64
     (2, 512, 1040, 128, [7, 31], 0, 0, 16),
     (5, 256, 528, 128, [20, 0, 0, 45, 1], 0, 0, 4),
     (6, 2048, 512, 128, [1, 1, 1, 1, 1, 1], 0, 0, -1),
@@ -993,6 +996,16 @@ def test_grouped_gemm_row_tile_heights(tm, oracle, E, K, N, g, counts, variant, 
     (4, 32, 4224, 1024, 32, 32 * 18, "skinny32x64"),      # long K in fine groups
     (8, 32, 2048, 1024, 32, 32 * 12, "tile32x128"),
     (8, 32, 2176, 1024, 32, 32 * 12, "skinny32x64"),
+    (4, 8, 256, 1024, 128, 8 * 16, "skinny16x16"),        # two 16-column tiles per CU: too few CTAs of 32 x 128
+    (4, 9, 256, 1024, 128, 9 * 16, "tile32x128"),
+    (4, 4, 7296, 1024, 128, 4 * 12, "skinny16x16"),
+    (4, 8, 8192, 1536, 128, 8 * 9, "skinny16x16"),        # strips of one column tile, K too long for the one-shot form
+    (8, 8, 256, 1024, 128, 8 * 15, "skinny16x16"),
+    (8, 8, 256, 1024, 128, 8 * 16, "tile32x128"),
+    (8, 4, 256, 1024, 128, 4 * 16, "skinny16x16"),
+    ("fp8", 8, 256, 1024, 128, 8 * 11, "skinny16x16"),
+    ("fp8", 8, 256, 1024, 128, 8 * 12, "tile32x128"),
+    ("fp8", 4, 256, 1024, 128, 4 * 12, "skinny32x64"),
     (4, 8, 256, 1024, 128, 8 * 40, "tile64x128"),
     (4, 8, 4096, 7168, 128, 8 * 700, "tile128x256"),
 ])
@@ -1001,8 +1014,11 @@ def test_grouped_gemm_shape_rule(tm, bits, E, K, N, g, rows, name):
     rng = np.random.default_rng(K + rows)
     if bits == 4:
         _, dev = _make_experts(tm, rng, 1, K, N, g)
-    else:
+    elif bits == 8:
         dev = [_pack_w8(tm, *_w8_case(rng, K, N, g), g)]
+    else:
+        q, s = _fp8_case(rng, K, N, g)
+        dev = [tm.tm_pack_w8_fp8(gu.to_dev(wl.pack_interchange8(q)), gu.to_dev(s), K, N, g)]
     group = tm.tm_group_experts(dev * E)
     assert tm.tm_variant_name(tm.tm_get_grouped_plan(group, rows)[0]) == name
     group.close()
