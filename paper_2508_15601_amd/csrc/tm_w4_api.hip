@@ -160,12 +160,13 @@ int ceil_div(int a, int b);
 
 // The CTA tile of a grouped launch, 64 x 128 or 128 x 256, from an estimate of both.  The rows per expert live on the device; a
 // balanced routing spreads them like counts of that mean, of which seven values stand for all experts.  A row tile that an
-// expert does not fill runs as one of 32, 64 or 96 rows.  The estimate is a least-squares fit to launches timed on both in turn (4-bit:
-// 2198, 8-bit formats: 1624; 4 ... 96 experts, K and N 1024 ... 14336 x 28672, mean 20 ... 900 rows, every group): a fixed part and, per 128
-// rows of K, of launches of at most one CTA per CU a part per CTA, per 16 rows of the longest CTA and per 16 rows and CU, of larger ones a
-// part per CTA and CU, per 16 rows and CU, and per round.  On as many others its choices are 0.2-2 % behind the faster of the two on
-// average (8-bit formats 1-3 %); 64 x 128 throughout is 3-7 % behind above 64 rows (8-10 %), 128 x 256 throughout 7-33 % (6-18 %).
-// 8 experts, 250 rows: 14336 x 4096 281 us on 64 x 128 tiles, 338 on 128 x 256; 1000 rows of 4096 x 7168: 480 and 437.
+// expert does not fill runs as one of 32, 64 or 96 rows.  The estimate is a least-squares fit to launches timed on both in turn (4-bit in
+// groups of 128, whose 64 x 128 tiles run four to a CU and all others three: 2434, else 2198, 8-bit formats: 1624; 1 ... 128 experts, K and
+// N 1024 ... 14336 x 28672, mean 19 ... 900 rows): a fixed part and, per 128 rows of K, of launches of at most one CTA per CU a part per CTA,
+// per 16 rows of the longest CTA and per 16 rows and CU, of larger ones a part per CTA and CU, per 16 rows and CU, and per round.  On 6458
+// others its choices are 0.3-1 % behind the faster of the two on average (8-bit formats 1-3 %) above a mean of 64 rows; 64 x 128 throughout
+// 0.4-9 % (8-10 %), 128 x 256 throughout 9-47 % (6-18 %).  Up to 64 rows 64 x 128 is at most 0.1 % behind (4-bit).
+// 8 experts, 250 rows: 14336 x 4096 279 us on 64 x 128 tiles, 343 on 128 x 256; 1000 rows of 4096 x 7168: 482 and 434.
 int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
 {
     struct Shape {
@@ -173,7 +174,9 @@ int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
         double one[4], more[4];         // us: fixed; then per 128 rows of K, in the order above
         double one32, more32;           // groups of 32: more per 128 rows of K
     };
-    static const Shape shapes[2][2] = {
+    static const Shape shapes[3][2] = {
+        {{kTile64x128, {3.790, 0.308, 0.050, 0.043}, {5.943, 0.037, 0.062, 0.285}, 0.0, 0.0},
+         {kTile128x256, {5.240, 0.627, 0.103, 0.094}, {6.933, 0.0, 0.177, 0.713}, 0.0, 0.0}},
         {{kTile64x128, {4.242, 0.283, 0.061, 0.032}, {6.128, 0.140, 0.062, 0.227}, 0.115, 0.044},
          {kTile128x256, {5.902, 0.580, 0.107, 0.104}, {9.803, 0.061, 0.172, 0.681}, 0.107, 0.053}},
         {{kTile64x128, {4.254, 0.285, 0.047, 0.055}, {5.065, 0.407, 0.0, 0.263}, 0.077, 0.060},
@@ -181,8 +184,9 @@ int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
     static const double spread[7] = {-1.5, -0.8, -0.4, 0.0, 0.4, 0.8, 1.5};
     const double mean = (double)total_rows / g->experts, dev = sqrt(mean), k = g->K / 128.0;
     int best = kTile64x128;
+    if (g->bits == 4 && mean <= 64.0) return best;
     double least = -1.0;
-    for (const Shape& s : shapes[g->bits == 8]) {
+    for (const Shape& s : shapes[g->bits == 8 ? 2 : g->group == 128 ? 0 : 1]) {
         const int bm = tile_bm(s.variant);
         double ctas = 0.0, heights = 0.0;           // row tiles, and their 16-row tiles
         int longest = 0;

@@ -1008,6 +1008,8 @@ def test_grouped_gemm_row_tile_heights(tm, oracle, E, K, N, g, counts, variant, 
     ("fp8", 4, 256, 1024, 128, 4 * 12, "skinny32x64"),
     (4, 8, 256, 1024, 128, 8 * 40, "tile64x128"),
     (4, 8, 4096, 7168, 128, 8 * 700, "tile128x256"),
+    (4, 13, 1792, 2832, 128, 13 * 521, "tile64x128"),     # four of its CTAs to a CU (83.6 us, 98.7 on 128 x 256)
+    (4, 8, 4096, 28672, 128, 8 * 64, "tile64x128"),
 ])
 def test_grouped_gemm_shape_rule(tm, bits, E, K, N, g, rows, name):
     """Which kernel the mean load of the experts asks for on 256 CUs."""
