@@ -728,7 +728,8 @@ Plan make_plan(const tm_packed_w4* h, int M, int num_cu)
             }
         }
         weigh_tile_shape_and_split(h, M, num_cu, KU, variant, split, pl);
-        if (!w8 && M > 64 && split == 1 && g_force_variant < 0 && g_force_split == 0 && g_force_waves == 0 && g_force_stage == 0) {
+        if (!w8 && M > 64 && split == 1 && g_force_variant < 0 && g_force_split == 0 && g_force_waves == 0 && g_force_stage == 0 &&
+            !(g_force_mfma == 32 && variant == kTile128x256)) {        // (asked for the 32x32x16 instruction: the tile that has it stays)
             one_set = lighter_tile(h, M, num_cu, variant);
             pl.variant = variant;
             pl.tiles_m = ceil_div(M, tile_bm(variant));

@@ -242,6 +242,25 @@ def test_tile_shape_of_several_ctas_per_cu(tm, oracle, M, K, N, g, name, block):
     packed.close()
 
 
+@pytest.mark.parametrize("M,K,N", [(900, 512, 12416), (900, 768, 14800)])
+def test_mfma_shape_request_keeps_the_prefill_tile(tm, oracle, M, K, N):
+    """A launch that the tile estimate moves from 128 x 256 to 64-row tiles stays there when the 32x32x16 instruction is asked for."""
+    d = _random_problem(M + K, M, K, N, 128)
+    packed = gu.pack(d, 128)
+    assert tm.tm_get_plan(packed, M)["name"] == "tile64x128"
+    tm.tm_set_mfma_shape(32)
+    try:
+        plan = tm.tm_get_plan(packed, M)
+        assert (plan["name"], plan["mfma_shape"]) == ("tile128x256", 32)
+        Y = gu.gemm(packed, d["X"])
+    finally:
+        tm.tm_set_mfma_shape(0)
+    rows = [0, 127, 128, M - 1]
+    ok, worst, fro = acceptance(Y[rows], oracle.gemm(d["X"][rows], d["q"], d["s"], d["z"], 128))
+    assert ok, (worst, fro)
+    packed.close()
+
+
 # The two prefill tiles exist with the 16x16x32 and with the 32x32x16 matrix instruction (the latter on request only):
 # both forms of both tiles, exact cases first.
 @pytest.mark.parametrize("shape", [16, 32])
