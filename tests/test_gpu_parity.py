@@ -823,7 +823,10 @@ GROUPED_CASES = [
     # E, K, N, g, rows per expert, rows before the first / after the last expert, forced variant (-1: library's choice)
     (4, 512, 272, 128, [0, 1, 17, 5], 0, 0, -1),
     (8, 1024, 2064, 64, [3, 0, 16, 2, 0, 0, 9, 1], 2, 3, -1),
-    (3, 256, 48, 32, [40, 0, 70], 0, 1, -1),            # average load picks the 64-row kernels; 70 rows = two passes
+    (3, 256, 48, 32, [40, 0, 70], 0, 1, -1),            # average load picks 64 x 128 tiles; 70 rows = two row tiles
+    (3, 256, 48, 32, [40, 0, 70], 0, 1, 19),            # 64-row decode kernel: 70 rows = two passes
+    (4, 640, 208, 128, [64, 65, 1, 130], 2, 0, 19),     # and three
+    (2, 384, 1040, 64, [129, 33], 0, 3, 19),
     (3, 256, 48, 32, [40, 0, 70], 1, 0, 0),             # 16-row kernel: five passes for the last expert
     (4, 512, 272, 128, [32, 16, 17, 5], 1, 2, -1),      # few CTAs: the 16-row kernels, two passes
     (2, 640, 144, 32, [33, 1], 0, 1, -1),               # and three
@@ -833,7 +836,8 @@ GROUPED_CASES = [
     (5, 256, 528, 128, [20, 0, 0, 45, 1], 0, 0, 4),
     (64, 256, 96, 128, [0] * 20 + [2] + [0] * 30 + [1, 5] + [0] * 11, 0, 0, -1),
     (6, 2048, 512, 128, [1, 1, 1, 1, 1, 1], 0, 0, -1),
-    # skewed routing: one expert holds nearly all rows, so the kernel chosen from the average load takes it in passes
+    # skewed routing: one expert holds nearly all rows, so the kernel chosen from the average load takes it in four row tiles (64 x 128),
+    # or in ten passes (16 rows)
     (8, 512, 272, 128, [200, 1, 0, 2, 0, 3, 1, 0], 0, 0, -1),
     (8, 512, 272, 64, [0, 0, 0, 0, 0, 0, 0, 150], 2, 0, -1),
     # prefill-sized loads go through the CTA-tile kernels (64x128, 128x256), also forced on small loads
@@ -929,6 +933,9 @@ GROUPED_8BIT_CASES = [
     (4, 512, 272, 128, [0, 1, 17, 5], 0, 0, -1),
     (8, 1024, 2064, 64, [3, 0, 16, 2, 0, 0, 9, 1], 2, 3, -1),
     (3, 256, 48, 32, [40, 0, 70], 0, 1, -1),
+    (3, 256, 48, 32, [40, 0, 70], 0, 1, 19),            # 64-row decode kernel: 70 rows = two passes
+    (4, 640, 208, 128, [64, 65, 1, 130], 2, 0, 19),     # and three
+    (2, 384, 1040, 64, [129, 33], 0, 3, 19),
     (4, 512, 272, 128, [32, 16, 17, 5], 1, 2, -1),      # few CTAs: int8 in two passes of the 16-row kernels, FP8 on 32 x 64
     (2, 512, 1040, 128, [7, 31], 0, 0, 16),
     (5, 256, 528, 128, [20, 0, 0, 45, 1], 0, 0, 4),
@@ -1042,6 +1049,38 @@ def test_grouped_gemm_shape_rule(tm, bits, E, K, N, g, rows, name):
         dev = [tm.tm_pack_w8_fp8(gu.to_dev(wl.pack_interchange8(q)), gu.to_dev(s), K, N, g)]
     group = tm.tm_group_experts(dev * E)
     assert tm.tm_variant_name(tm.tm_get_grouped_plan(group, rows)[0]) == name
+    group.close()
+    dev[0].close()
+
+
+@pytest.mark.parametrize("mean,name", [(12, "skinny32x64"), (40, "skinny64x64"), (100, None)])
+def test_grouped_gemm_more_activations_than_tile_offsets_reach(tm, oracle, mean, name):
+    """total_rows * K of 2^31 and more: the CTA tiles' 32-bit row offsets end there, the decode kernels take loads of up to 64 rows
+    (an expert with more rows in passes), larger loads are refused."""
+    import torch
+    K, N, g, rows = 16384, 48, 128, 132000
+    E = rows // mean
+    _say(f"grouped 2^31 E={E} K={K} N={N} rows={rows}")
+    host, dev = _make_experts(tm, np.random.default_rng(mean), 1, K, N, g)
+    group = tm.tm_group_experts(dev * E)
+    counts = np.full(E, mean)
+    counts[0], counts[-1] = 1, 2 * mean - 1
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    X = torch.zeros((rows, K), dtype=torch.float16, device="cuda")
+    Y = torch.full((rows, N), float("nan"), dtype=torch.float16, device="cuda")
+    if name is None:
+        with pytest.raises(tm.TmError):
+            tm.tm_gemm_w4a16_grouped(X, group, torch.from_numpy(offsets).cuda(), Y)
+    else:
+        assert tm.tm_variant_name(tm.tm_get_grouped_plan(group, rows)[0]) == name
+        some = [0, 1, mean, rows // 2, rows - 2 * mean, rows - 2 * mean + 1, rows - 20, rows - 1]
+        X[some] = torch.randn((len(some), K), dtype=torch.float16, device="cuda", generator=torch.Generator("cuda").manual_seed(mean))
+        tm.tm_gemm_w4a16_grouped(X, group, torch.from_numpy(offsets).cuda(), Y)
+        torch.cuda.synchronize()
+        ok, worst, fro = acceptance(Y[some].cpu().numpy(), oracle.gemm(X[some].cpu().numpy(), *host[0], g))
+        assert ok, (worst, fro)
+        Y[some] = 0
+        assert not Y.any()
     group.close()
     dev[0].close()
 
