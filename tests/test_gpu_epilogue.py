@@ -123,6 +123,10 @@ def test_epilogue_argument_checks(tm, oracle):
     (2, 512, 1056, 64, [16, 15], 2),
     (3, 512, 544, 128, [200, 0, 70], -1),                   # CTA tiles
     (4, 384, 160, 32, [130, 1, 0, 129], 9),
+    # every row-tile height at its edges, on 32 x 128 (scales on the fp32 sums), 64 x 128 and 128 x 256 tiles, a partial column tile
+    *[(9, K, N, g, [1, 32, 33, 64, 65, 96, 97, 128, 129], variant) for K, N, g in ((256, 288, 128), (384, 160, 64), (128, 544, 32))
+      for variant in (13, 9, 7)],
+    (4, 512, 288, 128, [31, 16, 17, 6], -1),                # the 16-row kernels in two passes
 ])
 def test_grouped_gemm_with_fused_activation(tm, oracle, E, K, N, g, counts, variant):
     """All experts of a mixture-of-experts layer in one launch, silu(gate)*up fused: per expert the oracle's product on
