@@ -76,8 +76,8 @@ __device__ __forceinline__ void wave_min_max(float& mn, float& mx)
 }
 
 // a / b rounded to nearest, exactly as the division gives it, from the correctly rounded reciprocal of b: a product and one
-// correction, three instructions where a division is ten.  Checked against the division for every finite fp16 a over every
-// finite positive fp16 b, and for every difference of two finite fp16 numbers over 15 and 255.
+// correction (Markstein), three instructions where a division is ten.  The tests check it against the division for every mantissa of an
+// fp16 value over every one of an fp16 scale, and for every fp32 mantissa over 15 and 255.
 __device__ __forceinline__ float quotient(float a, float b, float inv)
 {
     const float q = a * inv;
