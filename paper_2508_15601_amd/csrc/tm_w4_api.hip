@@ -583,8 +583,9 @@ static void weigh_tile_shape_and_split(const tm_packed_w4* h, int M, int num_cu,
 }
 
 // Unsplit launches of 4-bit layers above 64 rows: the shape chosen so far (128 x 256, 128 x 128 or 64 x 128) against two that the
-// rules above do not weigh, 64 x 96 and 64 x 128 with one wave set per CTA.  Their CTAs of four waves share a CU by three or four, so a
-// launch of several CTAs per CU ends more evenly and hides a CTA's start and end behind the others.  The estimate is a least-squares
+// rules above do not weigh, 64 x 96 and 64 x 128 with one wave set per CTA.  Their CTAs of four waves share a CU by three (64 x 128, 129 to
+// 144 registers; 64 x 96 with 64-deep stages) or two (64 x 96 with 128-deep stages, 174 to 196 registers), so a launch of several CTAs per
+// CU ends more evenly and hides a CTA's start and end behind the others.  The estimate is a least-squares
 // fit to timed unsplit plans of 7138 random layers (K 1024 ... 28672, N 1024 ... 32768, M 65 ... 4096, every group; rms error 3-5 %): a
 // fixed part and, per 128 rows of K, of launches of at most one CTA per CU a part and one by the load, of larger ones parts by the
 // load, by whole rounds of one and of two CTAs per CU; more where groups of 32 make four times the scales, and the output's store.
