@@ -165,7 +165,8 @@ int ceil_div(int a, int b);
 // N 1024 ... 14336 x 28672, mean 19 ... 900 rows): a fixed part and, per 128 rows of K, of launches of at most one CTA per CU a part per CTA,
 // per 16 rows of the longest CTA and per 16 rows and CU, of larger ones a part per CTA and CU, per 16 rows and CU, and per round.  On 6458
 // others its choices are 0.3-1 % behind the faster of the two on average (8-bit formats 1-3 %) above a mean of 64 rows; 64 x 128 throughout
-// 0.4-9 % (8-10 %), 128 x 256 throughout 9-47 % (6-18 %).  Up to 64 rows 64 x 128 is at most 0.1 % behind (4-bit).
+// 0.4-9 % (8-10 %), 128 x 256 throughout 9-47 % (6-18 %).  Up to 64 rows 64 x 128 is 0.1 % behind (4-bit; 0.7 % at 60 ... 64 rows in
+// groups of 64 and 32).
 // 8 experts, 250 rows: 14336 x 4096 279 us on 64 x 128 tiles, 343 on 128 x 256; 1000 rows of 4096 x 7168: 482 and 434.
 int grouped_tile(const tm_expert_group* g, int total_rows, int num_cu)
 {
