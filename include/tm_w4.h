@@ -237,8 +237,9 @@ TM_API void tm_free_packed(tm_packed_w4* packed);
  * from total_rows / num_experts (the per-expert counts are not known on the host): decode-sized loads run the decode
  * kernels (an expert with more rows than one pass takes, 16-64, is processed in several passes), larger loads the
  * CTA-tile kernels, which need total_rows * K < 2^31: from about 64 rows per expert on a call beyond that is refused,
- * below it runs the decode kernels.  The choice assumes a roughly balanced routing (mean load plus three standard deviations); under a heavily skewed one the result
- * is still exact, but an expert with many times the average load is taken in passes that each stream its weights again.
+ * below it runs the decode kernels.  The choice assumes a roughly balanced routing (mean load plus three standard
+ * deviations); under a heavily skewed one the result is still exact, but an expert with many times the average load is
+ * taken in passes that each stream its weights again.
  * total_rows == 0 is a successful no-op; total_rows < 2^24.
  */
 typedef struct tm_expert_group tm_expert_group;
